@@ -94,8 +94,8 @@ typedef struct fpic_tuning {
                                 the data a stage does not read again soon,
                                 which pays when one box's arrays overflow the
                                 256 MB Infinity Cache; 0 chooses by size
-                                (streaming for a single box of >= 64 MB of
-                                state).  3D boxes always stream. */
+                                (streaming for a single box of 176 to 320 MB
+                                of state).  3D boxes always stream. */
     int32_t fused;           /* 3D boxes with the linear shape: 0 or 1 one
                                 kernel per stage that also deposits, through
                                 per-workgroup partial rows and a small

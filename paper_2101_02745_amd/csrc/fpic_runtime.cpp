@@ -134,6 +134,61 @@ int validate_1d(const fpic_config &c, int idx)
 
 bool is_1d(const fpic_config &c) { return c.ncell[0] == 1 && c.ncell[1] == 1; }
 
+// The launch shape where the caller leaves it open (waves or dpw zero).  A
+// workgroup stages its grid tiles and sums its waves' deposits once, about as
+// long as kFixed directions take, and each of its waves sweeps dpw
+// directions; the chip holds 8 waves per CU (the stage kernels use 211-254
+// registers), so a launch takes ceil(workgroups / slots) rounds of dpw +
+// kFixed.  The shape with the fewest is taken: up to one workgroup of 8 waves
+// on each of the 256 CUs, then longer waves.  Against 4 waves and about 1024
+// workgroups, us per step: 2048 x 378 285 -> 202, 1000 x 378 209 -> 137,
+// 4096 x 128 239 -> 164, 512 x 128 90 -> 81, 777 x 92 quadratic 147 -> 116,
+// 5000 x 378 565 -> 467, 24 boxes of 11.5 M particles 3958 -> 3094 (those
+// measured fastest in a sweep of 1-8 waves and 1-24 directions).  Workgroups
+// of 4 waves stage twice as many tiles per CU (219 us for the 2048 x 378 box)
+// and pay where their smaller granularity saves a round.  A single box gets
+// at most the workgroups (and partial sums) of 4 waves in about 1024 of them:
+// fpic_step_noalloc's fixed scratch, which takes the same shape, holds every
+// box up to the size its limit states.
+void choose_shape(int nsim, const fpic_config *cfgs, int &waves, int &dpw)
+{
+    constexpr int kCus = 256;
+    const bool w_open = waves == 0, d_open = dpw == 0;
+    int64_t most = INT64_MAX;
+    if (nsim == 1 && w_open && d_open) {
+        const int64_t ntile = (cfgs[0].ncell[2] + TILE - 1) / TILE, nd = cfgs[0].ndir;
+        const int64_t dpg = 4 * std::max<int64_t>(1, std::min<int64_t>(64, (ntile * nd + 4095) / 4096));
+        most = ntile * ((nd + dpg - 1) / dpg);
+    }
+    double best = 1e300;
+    int bw = w_open ? 8 : waves, bd = d_open ? 32 : dpw;
+    for (int w : {8, 4}) {
+        if (!w_open && w == 4)
+            break;  // the caller's waves, once
+        const int wv = w_open ? w : waves;
+        for (int d : {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32}) {
+            if (!d_open && d > 1)
+                break;  // the caller's dpw, once
+            const int dp = d_open ? d : dpw;
+            int64_t wg = 0;
+            for (int i = 0; i < nsim; ++i) {
+                const int64_t dpg = (int64_t)wv * std::min(dp, cfgs[i].ndir);
+                wg += (int64_t)((cfgs[i].ncell[2] + TILE - 1) / TILE) * ((cfgs[i].ndir + dpg - 1) / dpg);
+            }
+            const int64_t slots = (int64_t)kCus * 8 / wv;
+            const double fixed = wv >= 8 ? 1.5 : 2.5;
+            const double cost = (double)((wg + slots - 1) / slots) * (dp + fixed);
+            if (wg <= most && cost < best) {
+                best = cost;
+                bw = wv;
+                bd = dp;
+            }
+        }
+    }
+    waves = bw;
+    dpw = bd;
+}
+
 // external_state: the state array is the caller's (no room for it in the
 // workspace); used by the entry point that allocates nothing.
 int make_plan(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, Plan &P,
@@ -153,8 +208,8 @@ int make_plan(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, Plan &
     P = Plan();
     P.nsim = nsim;
     P.shape = cfgs[0].shape_order;
-    P.waves = (tune && tune->waves) ? tune->waves : 4;
-    if (P.waves != 1 && P.waves != 2 && P.waves != 4 && P.waves != 8)
+    P.waves = tune ? tune->waves : 0;
+    if (P.waves != 0 && P.waves != 1 && P.waves != 2 && P.waves != 4 && P.waves != 8)
         return fail(FPIC_EINVAL, "waves must be 1, 2, 4 or 8");
     P.spg = (tune && tune->steps_per_graph) ? tune->steps_per_graph : 8;
     if (P.spg < 1 || P.spg > 256)
@@ -163,11 +218,16 @@ int make_plan(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, Plan &
     if (policy < 0 || policy > 2)
         return fail(FPIC_EINVAL, "cache_policy must be 0, 1 or 2");
     if (policy == 0) {
-        // streaming pays when one box's arrays overflow the 256 MB Infinity
-        // Cache (measured: the 2048 x 378 box gains 14%, a 512 x 128 box and
-        // the 64-box batch lose 2-4%)
-        const int64_t np0 = (int64_t)cfgs[0].ncell[2] * cfgs[0].ndir;
-        P.nt = nsim == 1 && np0 * 18 * (int64_t)sizeof(double) >= (int64_t)64 << 20;
+        // Streaming pays where one box's state nearly fills or just
+        // overflows the 256 MB Infinity Cache.  Default against streaming,
+        // us per step in the built-in launch shape: 111 MB (2048 x 378) 202
+        // against 217, 163 MB (3000 x 378) equal, 218 MB (4000 x 378) 381
+        // against 361, 272 MB (5000 x 378) 489 against 467, 381 MB (7000 x
+        // 378) 700 against 705; batches, whose boxes are swept one after
+        // another, gain nothing (24 boxes, 11.5 M particles: 3094 against
+        // 3131).
+        const int64_t state0 = (int64_t)cfgs[0].ncell[2] * cfgs[0].ndir * 18 * (int64_t)sizeof(double);
+        P.nt = nsim == 1 && state0 >= (int64_t)176 << 20 && state0 <= (int64_t)320 << 20;
     } else {
         P.nt = policy == 2;
     }
@@ -175,17 +235,10 @@ int make_plan(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, Plan &
     if (fused < 0 || fused > 2)
         return fail(FPIC_EINVAL, "fused must be 0, 1 or 2");
     P.rk = 2 - fused;
-    int64_t wavedirs = 0;
-    for (int i = 0; i < nsim; ++i)
-        wavedirs += (int64_t)((cfgs[i].ncell[2] + TILE - 1) / TILE) * cfgs[i].ndir;
     int dpw = (tune && tune->dirs_per_wave) ? tune->dirs_per_wave : 0;
     if (dpw < 0 || dpw > 256)
         return fail(FPIC_EINVAL, "dirs_per_wave must be in 0..256");
-    if (!dpw) {
-        // aim at about 1024 workgroups in total
-        const int64_t target = 1024LL * P.waves;
-        dpw = (int)std::max<int64_t>(1, std::min<int64_t>(64, (wavedirs + target - 1) / target));
-    }
+    choose_shape(nsim, cfgs, P.waves, dpw);
     Carver cv;
     P.sims.resize(nsim);
     for (int i = 0; i < nsim; ++i) {
