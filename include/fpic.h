@@ -110,7 +110,9 @@ typedef struct fpic_tuning {
                                 instead of stored and read back.  1: stage 1
                                 stores no slope, stages 2 and 4 form k1;
                                 0: stage 2 stores none either, stages 3 and
-                                4 form k1 and k2; 2: every slope stored.
+                                4 form k1 and k2 (small boxes, with one
+                                direction per wave: as is fastest, and whole
+                                steps in one launch); 2: every slope stored.
                                 Bitwise the same results.  Per particle-step
                                 1360, 976 and 1744 B. */
 } fpic_tuning;

@@ -30,162 +30,11 @@
 // floor(u) is the integer shift, u - floor(u) the CIC fraction.  Stage times
 // are t = n dt + c_s dt (c_s = 0, 1/2, 1/2, 1), each operation rounded once,
 // exactly as the CPU reference forms them.
-#include "fpic_device.h"
-#include "fpic_internal.h"
+#include <algorithm>
+
+#include "fpic_1d_body.h"
 
 namespace fpic {
-
-struct Shift {
-    int64_t i;
-    double phi;
-};
-
-__device__ __forceinline__ Shift shift_of(double v, double t, double dx)
-{
-#pragma clang fp contract(off)
-    const double u = (v * t) / dx;
-    const double fl = floor(u);
-    Shift s;
-    s.i = (int64_t)fl;
-    s.phi = u - fl;
-    return s;
-}
-
-// Value of the lane one below (lane 0 receives 0): DPP wave_shr:1 on the two
-// 32-bit halves, no LDS traffic.
-__device__ __forceinline__ double lane_below(double x)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x138, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x138, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-
-// Value of the lane one above (lane 63 receives 0): DPP wave_shl:1.
-__device__ __forceinline__ double lane_above(double x)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x130, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x130, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ int pmod_i64(int64_t a, int n)
-{
-    int64_t r = a % n;
-    return (int)(r < 0 ? r + n : r);
-}
-
-// r = i mod n for an integer-valued double i (|i| < 2^52), without 64-bit
-// integer division.
-__device__ __forceinline__ int pmod_dbl(double i, int n)
-{
-    const double nd = (double)n;
-    double r = i - nd * floor(i / nd);
-    if (r < 0.0)
-        r += nd;
-    if (r >= nd)
-        r -= nd;
-    return (int)r;
-}
-
-// The slope path of the 1D stages (gather, Hamiltonians, commutators) is
-// written with explicit fused multiply-adds and no other contraction, so a
-// slope formed again in a later stage rounds exactly as where it was first
-// formed, whatever the surrounding code lets the compiler fuse.
-
-// Neutrino self-interaction part of H at a particle (eq. potentials,
-// interpolated with eq. pic_interpolation): the four staged moment groups
-// n - nbar^*, f_x, f_y, f_z - fbar^* of the tile Gt (stride gts per
-// component) at column kl and fraction phi, combined as n - v.f.
-template <int SH>
-__device__ __forceinline__ void gather_hnn(const double *Gt, int gts, int kl, double phi, double vx,
-                                           double vy, double vz, double Hnn[9])
-{
-#pragma clang fp contract(off)
-    if (SH == 2) {
-        const Quad q = quad_weights(phi);
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            const double *g = Gt + k * gts + kl - 1 + q.up;
-            double B[4];
-#pragma unroll
-            for (int c = 0; c < 4; c++) {
-                const double *h = g + 9 * c * gts;
-                B[c] = __builtin_fma(q.w2, h[2], __builtin_fma(q.w1, h[1], q.w0 * h[0]));
-            }
-            Hnn[k] = __builtin_fma(-vz, B[3], __builtin_fma(-vy, B[2], __builtin_fma(-vx, B[1], B[0])));
-        }
-    } else {
-        const double omp = 1.0 - phi;
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            const double *g = Gt + k * gts + kl;
-            double B[4];
-#pragma unroll
-            for (int c = 0; c < 4; c++) {
-                const double *h = g + 9 * c * gts;
-                B[c] = __builtin_fma(phi, h[1], omp * h[0]);
-            }
-            Hnn[k] = __builtin_fma(-vz, B[3], __builtin_fma(-vy, B[2], __builtin_fma(-vx, B[1], B[0])));
-        }
-    }
-}
-
-// -i [H, rho] for Hermitian H and rho packed as 9 reals (diagonal, then
-// Re/Im of the (0,1), (0,2), (1,2) entries), the same packing and slope as
-// commutator() of the shared helpers, each sum of products written as one
-// chain of fused multiply-adds.
-__device__ __forceinline__ void commutator_fma(const double h[9], const double r[9], double k[9])
-{
-#pragma clang fp contract(off)
-    const double h0 = h[0], h1 = h[1], h2 = h[2];
-    const double ar = h[3], ai = h[4], br = h[5], bi = h[6], cr = h[7], ci = h[8];
-    const double p0 = r[0], p1 = r[1], p2 = r[2];
-    const double xr = r[3], xi = r[4], yr = r[5], yi = r[6], zr = r[7], zi = r[8];
-    const double k1 = 2.0 * (__builtin_fma(ar, xi, -(ai * xr)) + __builtin_fma(ci, zr, -(cr * zi)));
-    const double k2 = 2.0 * (__builtin_fma(br, yi, -(bi * yr)) + __builtin_fma(cr, zi, -(ci * zr)));
-    k[1] = k1;
-    k[2] = k2;
-    k[0] = -(k1 + k2);
-    // C01 = h0 x + a p1 + b z^*,  C10 = a^* p0 + h1 x^* + c y^*
-    const double c01r = __builtin_fma(h0, xr, __builtin_fma(ar, p1, __builtin_fma(br, zr, bi * zi)));
-    const double c01i = __builtin_fma(h0, xi, __builtin_fma(ai, p1, __builtin_fma(bi, zr, -(br * zi))));
-    const double c10r = __builtin_fma(ar, p0, __builtin_fma(h1, xr, __builtin_fma(cr, yr, ci * yi)));
-    const double c10i = __builtin_fma(-ai, p0, __builtin_fma(-h1, xi, __builtin_fma(ci, yr, -(cr * yi))));
-    k[3] = c01i + c10i;
-    k[4] = c10r - c01r;
-    // C02 = h0 y + a z + b p2,  C20 = b^* p0 + c^* x^* + h2 y^*
-    const double c02r = __builtin_fma(h0, yr, __builtin_fma(ar, zr, __builtin_fma(-ai, zi, br * p2)));
-    const double c02i = __builtin_fma(h0, yi, __builtin_fma(ar, zi, __builtin_fma(ai, zr, bi * p2)));
-    const double c20r = __builtin_fma(br, p0, __builtin_fma(cr, xr, __builtin_fma(-ci, xi, h2 * yr)));
-    const double c20i = __builtin_fma(-bi, p0, __builtin_fma(-cr, xi, __builtin_fma(-ci, xr, -(h2 * yi))));
-    k[5] = c02i + c20i;
-    k[6] = c20r - c02r;
-    // C12 = a^* y + h1 z + c p2,  C21 = b^* x + c^* p1 + h2 z^*
-    const double c12r = __builtin_fma(ar, yr, __builtin_fma(ai, yi, __builtin_fma(h1, zr, cr * p2)));
-    const double c12i = __builtin_fma(ar, yi, __builtin_fma(-ai, yr, __builtin_fma(h1, zi, ci * p2)));
-    const double c21r = __builtin_fma(br, xr, __builtin_fma(bi, xi, __builtin_fma(cr, p1, h2 * zr)));
-    const double c21i = __builtin_fma(br, xi, __builtin_fma(-bi, xr, __builtin_fma(-ci, p1, -(h2 * zi))));
-    k[7] = c12i + c21i;
-    k[8] = c21r - c12r;
-}
-
-// Slopes of rho and rhobar (eq. eom): H = Hvac + Hmat + Hnn and
-// Hbar = (Hvac - Hmat - Hnn)^*, hv and hvb holding Hvac + Hmat and
-// Hvac - Hmat packed.
-__device__ __forceinline__ void slope_of(const double hv[9], const double hvb[9], const double Hnn[9],
-                                         const double y[18], double kk[18])
-{
-#pragma clang fp contract(off)
-    double H[9], Hb[9];
-#pragma unroll
-    for (int k = 0; k < 9; k++) {
-        H[k] = hv[k] + Hnn[k];
-        const double hb = hvb[k] - Hnn[k];
-        Hb[k] = (k == 4 || k == 6 || k == 8) ? -hb : hb;
-    }
-    commutator_fma(H, y, kk);
-    commutator_fma(Hb, y + 9, kk + 9);
-}
 
 // NT: streaming (nontemporal) cache policy for the data a stage does not
 // read again soon (the last reads of the slopes in stage 4, and k2); the
@@ -248,7 +97,7 @@ stage1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ si
     }
 
     // LDS: [grid tile | reduction] [edge buffers] [per-direction shifts]
-    const int gslot = max(NG * GTS, NG * TILE + nwaves * NG * NE);
+    const int gslot = max(NG * GTS, red_doubles(nwaves, NE));
     double *Gt = smem;                                        // [NG][GTS]
     double *eb = smem + gslot + wave * max_dpw * 9 * NE;      // [dpw][NE][9] of this wave
     double *tphi = smem + gslot + nwaves * max_dpw * 9 * NE;  // [dpg][2]: phi_cur, phi_nxt
@@ -486,106 +335,11 @@ stage1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ si
                 X[k] = 0.0;
         }
 
-        if (SH == 2) {
-            // quadratic deposit with the next-stage weights: the particle at
-            // anchor m feeds cells m - 1 + up' .. m + 1 + up', so cell m
-            // takes w0' w1' w2' of lanes (m + 1, m, m - 1) when up' = 0 and
-            // of lanes (m, m - 1, m - 2) when up' = 1 (one-lane DPP moves);
-            // what leaves the tile goes to the edge partials: one cell on
-            // the left (lane 0), two on the right (the last active lanes)
-            const Quad q = quad_weights(ph);
-#pragma unroll
-            for (int k = 0; k < 9; k++) {
-                const double x = X[k];
-                double s1 = lane_below(x);
-                s1 = (lane == 0) ? 0.0 : s1;
-                double a, b, c;
-                if (q.up) {
-                    double s2 = lane_below(s1);
-                    s2 = (lane == 0) ? 0.0 : s2;
-                    a = x;
-                    b = s1;
-                    c = s2;
-                } else {
-                    double xa = lane_above(x);
-                    xa = (lane == TILE - 1) ? 0.0 : xa;
-                    a = xa;
-                    b = x;
-                    c = s1;
-                }
-                const double xc = wsum3(q.w0, a, q.w1, b, q.w2, c);
-                acc[k] += xc;
-                acc[9 + k] += vx * xc;
-                acc[18 + k] += vy * xc;
-                acc[27 + k] += vz * xc;
-                if (lane == nact - 1) {
-                    eb[((d - dbeg) * NE + 0) * 9 + k] = q.up ? wsum2(q.w1, x, q.w2, s1) : q.w2 * x;
-                    eb[((d - dbeg) * NE + 1) * 9 + k] = q.up ? q.w2 * x : 0.0;
-                }
-                if (lane == 0)
-                    eb[((d - dbeg) * NE + 2) * 9 + k] = q.up ? 0.0 : q.w0 * x;
-            }
-        } else {
-            // deposit with the next-stage weights: cell m gets (1 - phi') of
-            // its own particle and phi' of the particle one lane to the left
-            const double omph = 1.0 - ph;
-#pragma unroll
-            for (int k = 0; k < 9; k++) {
-                double xl = lane_below(X[k]);
-                xl = (lane == 0) ? 0.0 : xl;
-                const double xc = wsum2(omph, X[k], ph, xl);
-                acc[k] += xc;
-                acc[9 + k] += vx * xc;
-                acc[18 + k] += vy * xc;
-                acc[27 + k] += vz * xc;
-            }
-            if (lane == nact - 1) {
-#pragma unroll
-                for (int k = 0; k < 9; k++)
-                    eb[(d - dbeg) * 9 + k] = ph * X[k];
-            }
-        }
+        deposit_dir<SH>(X, ph, vx, vy, vz, lane, nact, acc, eb + (d - dbeg) * 9 * NE);
     }
 
-    // ---- workgroup reduction (fixed order over waves) -----------------
-    __syncthreads();  // the grid tile is no longer needed: reuse it
-    double *redb = smem;  // [NG][TILE]
-    for (int w = 0; w < nwaves; ++w) {
-        if (wave == w) {
-#pragma unroll
-            for (int k = 0; k < NG; k++)
-                redb[k * TILE + lane] = (w == 0) ? acc[k] : redb[k * TILE + lane] + acc[k];
-        }
-        __syncthreads();
-    }
-    // edge partials of each wave: one lane per (edge, moment component)
-    // sums over the wave's directions
-    double *esum = smem + NG * TILE;  // [nwaves][NE][NG]
-    for (int q = lane; q < NE * NG; q += TILE) {
-        const int e = q / NG, r = q - e * NG;
-        const int comp = r % 9, grp = r / 9;
-        double s = 0.0;
-        for (int d = dbeg; d < dend; ++d) {
-            const double coef = (grp == 0) ? 1.0 : (grp == 1) ? tld(S.vx, d) : (grp == 2) ? tld(S.vy, d) : tld(S.vz, d);
-            s += coef * eb[((d - dbeg) * NE + e) * 9 + comp];
-        }
-        esum[(wave * NE + e) * NG + r] = s;
-    }
-    __syncthreads();
-
-    const int ntc = S.ntile * TILE;
-    double *part = S.part + (size_t)wi.group * NG * ntc;
-    for (int idx = threadIdx.x; idx < NG * TILE; idx += blockDim.x) {
-        const int k = idx / TILE, l = idx - k * TILE;
-        gst(part + (size_t)k * ntc + tile0 + l, redb[idx]);
-    }
-    for (int q = threadIdx.x; q < NE * NG; q += blockDim.x) {
-        const int e = q / NG, r = q - e * NG;
-        double s = 0.0;
-        for (int w = 0; w < nwaves; ++w)
-            s += esum[(w * NE + e) * NG + r];
-        gst(S.edge + (((size_t)wi.group * NG + r) * NE + e) * S.ntile + wi.tile, s);
-    }
+    // ---- workgroup reduction (the grid tiles are no longer needed)
+    wg_reduce<SH>(S, wi, acc, eb, dbeg, dend, 1.0, smem, wave, lane, nwaves);
 }
 
 // ---------------------------------------------------------------------------
@@ -652,7 +406,7 @@ adj1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ sims
 
     // LDS: [Gamma tile | reduction] [stage-SA grid tile] [edge buffers]
     //      [phi_anchor, phi_B per direction] [r, delta per direction]
-    const int gslot = max(NG * GTS, NG * TILE + nwaves * NG * NE);
+    const int gslot = max(NG * GTS, red_doubles(nwaves, NE));
     double *GtB = smem;
     double *GtA = smem + gslot;
     double *eb = smem + 2 * gslot + wave * max_dpw * 9 * NE;
@@ -873,100 +627,16 @@ adj1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ sims
                 for (int k = 0; k < 9; k++)
                     X[k] = 0.0;
             }
-            if (SH == 2) {
-                // quadratic deposit at t_SA, as in the stage kernels
-                const Quad q = quad_weights(phA);
-#pragma unroll
-                for (int k = 0; k < 9; k++) {
-                    const double x = X[k];
-                    double s1 = lane_below(x);
-                    s1 = (lane == 0) ? 0.0 : s1;
-                    double a, b, cc;
-                    if (q.up) {
-                        double s2 = lane_below(s1);
-                        s2 = (lane == 0) ? 0.0 : s2;
-                        a = x;
-                        b = s1;
-                        cc = s2;
-                    } else {
-                        double xa = lane_above(x);
-                        xa = (lane == TILE - 1) ? 0.0 : xa;
-                        a = xa;
-                        b = x;
-                        cc = s1;
-                    }
-                    const double xc = (q.w0 * a + q.w1 * b) + q.w2 * cc;
-                    acc[k] += xc;
-                    acc[9 + k] -= vx * xc;
-                    acc[18 + k] -= vy * xc;
-                    acc[27 + k] -= vz * xc;
-                    if (lane == nact - 1) {
-                        eb[((d - dbeg) * NE + 0) * 9 + k] = q.up ? q.w1 * x + q.w2 * s1 : q.w2 * x;
-                        eb[((d - dbeg) * NE + 1) * 9 + k] = q.up ? q.w2 * x : 0.0;
-                    }
-                    if (lane == 0)
-                        eb[((d - dbeg) * NE + 2) * 9 + k] = q.up ? 0.0 : q.w0 * x;
-                }
-            } else {
-                // deposit the sources at t_SA: cell m gets (1 - phi) of its
-                // own particle and phi of the particle one lane to the left
-#pragma unroll
-                for (int k = 0; k < 9; k++) {
-                    double xl = lane_below(X[k]);
-                    xl = (lane == 0) ? 0.0 : xl;
-                    const double xc = omA * X[k] + phA * xl;
-                    acc[k] += xc;
-                    acc[9 + k] -= vx * xc;
-                    acc[18 + k] -= vy * xc;
-                    acc[27 + k] -= vz * xc;
-                }
-                if (lane == nact - 1) {
-#pragma unroll
-                    for (int k = 0; k < 9; k++)
-                        eb[(d - dbeg) * 9 + k] = phA * X[k];
-                }
-            }
+            // deposit at t_SA with the forward weights; the flux groups take
+            // the sources with the opposite sign
+            deposit_dir<SH>(X, phA, -vx, -vy, -vz, lane, nact, acc, eb + (d - dbeg) * 9 * NE);
         }
     }
     if (!DO_A)
         return;
 
     // ---- workgroup reduction of the deposited sources (as in the stages)
-    __syncthreads();
-    double *redb = smem;
-    for (int w = 0; w < nwaves; ++w) {
-        if (wave == w) {
-#pragma unroll
-            for (int k = 0; k < NG; k++)
-                redb[k * TILE + lane] = (w == 0) ? acc[k] : redb[k * TILE + lane] + acc[k];
-        }
-        __syncthreads();
-    }
-    double *esum = smem + NG * TILE;  // [nwaves][NE][NG]
-    for (int q = lane; q < NE * NG; q += TILE) {
-        const int e = q / NG, r = q - e * NG;
-        const int comp = r % 9, grp = r / 9;
-        double sacc = 0.0;
-        for (int d = dbeg; d < dend; ++d) {
-            const double coef = (grp == 0) ? 1.0 : (grp == 1) ? -tld(S.vx, d) : (grp == 2) ? -tld(S.vy, d) : -tld(S.vz, d);
-            sacc += coef * eb[((d - dbeg) * NE + e) * 9 + comp];
-        }
-        esum[(wave * NE + e) * NG + r] = sacc;
-    }
-    __syncthreads();
-    const int ntc = S.ntile * TILE;
-    double *part = S.part + (size_t)wi.group * NG * ntc;
-    for (int idx = threadIdx.x; idx < NG * TILE; idx += blockDim.x) {
-        const int k = idx / TILE, l = idx - k * TILE;
-        gst(part + (size_t)k * ntc + tile0 + l, redb[idx]);
-    }
-    for (int q = threadIdx.x; q < NE * NG; q += blockDim.x) {
-        const int e = q / NG, r = q - e * NG;
-        double sacc = 0.0;
-        for (int w = 0; w < nwaves; ++w)
-            sacc += esum[(w * NE + e) * NG + r];
-        gst(S.edge + (((size_t)wi.group * NG + r) * NE + e) * S.ntile + wi.tile, sacc);
-    }
+    wg_reduce<SH>(S, wi, acc, eb, dbeg, dend, -1.0, smem, wave, lane, nwaves);
 }
 
 __global__ void fill_kernel(double *p, size_t n, double v)
@@ -986,84 +656,20 @@ reduce1d_kernel(const RedItem *__restrict__ items, const SimDesc *__restrict__ s
 {
     const RedItem it = items[blockIdx.x];
     const SimDesc &S = sims[it.sim];
-    const int nc = S.ncell, ntile = S.ntile, ntc = ntile * TILE;
+    const int nc = S.ncell;
     const int tile0 = it.tile * TILE;
     const int nact = min(TILE, nc - tile0);
     double *out = (which <= 4) ? S.G[which] : (which == RED_GA) ? S.GA : override_out;
     const int k = blockIdx.y * 4 + (threadIdx.x >> 6);
     const int l = threadIdx.x & (TILE - 1);
     if (l < nact) {
-        const int ng = S.ngroup;
-        const double *pp = S.part + (size_t)k * ntc + tile0 + l;
-        const size_t gstride = (size_t)NG * ntc;
-        // loads in flight together, sums in group order
-        double s = 0.0;
-        int g = 0;
-        for (; g + 8 <= ng; g += 8) {
-            double v[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                v[q] = gld(pp + (size_t)(g + q) * gstride);
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                s += v[q];
-        }
-        for (; g < ng; ++g)
-            s += gld(pp + (size_t)g * gstride);
-        if (S.shape == 2) {
-            // quadratic: a tile's right-edge cells are the first two after
-            // it (the second lies two tiles on when the next tile has one
-            // cell), its left-edge cell the last before it; with one tile
-            // or very few cells they fold onto the tile itself.  Candidate
-            // sources in a fixed order: tiles T-2, T-1, T, T+1 (each once).
-            const int j = tile0 + l;
-            int cand[4] = {(it.tile + 2 * ntile - 2) % ntile, (it.tile + ntile - 1) % ntile, it.tile,
-                           (it.tile + 1) % ntile};
-            for (int ci = 0; ci < 4; ++ci) {
-                const int src = cand[ci];
-                bool seen = false;
-                for (int cj = 0; cj < ci; ++cj)
-                    seen = seen || (cand[cj] == src);
-                if (seen)
-                    continue;
-                const int t0s = src * TILE, nas = min(TILE, nc - t0s);
-                for (int e = 0; e < 3; ++e) {
-                    const int target = (e < 2) ? (t0s + nas + e) % nc : (t0s + nc - 1) % nc;
-                    if (target != j)
-                        continue;
-                    const double *ep = S.edge + ((size_t)k * 3 + e) * ntile + src;
-                    const size_t estride = (size_t)NG * 3 * ntile;
-                    int g2 = 0;
-                    for (; g2 + 8 <= ng; g2 += 8) {
-                        double v[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q)
-                            v[q] = gld(ep + (size_t)(g2 + q) * estride);
-#pragma unroll
-                        for (int q = 0; q < 8; ++q)
-                            s += v[q];
-                    }
-                    for (; g2 < ng; ++g2)
-                        s += gld(ep + (size_t)g2 * estride);
-                }
-            }
-        } else if (l == 0) {
-            const int tprev = (it.tile + ntile - 1) % ntile;
-            const double *ep = S.edge + (size_t)k * ntile + tprev;
-            const size_t estride = (size_t)NG * ntile;
-            int g2 = 0;
-            for (; g2 + 8 <= ng; g2 += 8) {
-                double v[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    v[q] = gld(ep + (size_t)(g2 + q) * estride);
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    s += v[q];
-            }
-            for (; g2 < ng; ++g2)
-                s += gld(ep + (size_t)g2 * estride);
-        }
+        // the groups, then each edge source
+        const int ng = S.ngroup, ntile = S.ntile;
+        const int ne = n_edges(S.shape);
+        double s = group_sum(S.part + (size_t)k * ntile * TILE + tile0 + l, ng, (size_t)NG * ntile * TILE);
+        edge_sources(S.shape, nc, ntile, it.tile, l, [&](int src, int e) {
+            s += group_sum(S.edge + ((size_t)k * ne + e) * ntile + src, ng, (size_t)NG * ne * ntile);
+        });
         out[(size_t)k * nc + tile0 + l] = s;
     }
     if (tick && it.tile == 0 && blockIdx.y == 0 && threadIdx.x == 0)
@@ -1196,15 +802,13 @@ __global__ void fill_state_kernel(const SimDesc *sims, int sim)
             S.Y[k * S.np + p] = (k == 0 || k == 9) ? 1.0 : 0.0;
 }
 
-size_t stage1d_smem_bytes(int waves, int max_dpw, int shape)
+// LDS of a stage or adjoint workgroup with nslot slots for a grid tile (the
+// first shared with the reduction's buffer) and the per-direction data.
+static size_t smem1d_bytes(int waves, int max_dpw, int shape, int nslot)
 {
-    const size_t ne = n_edges(shape);
-    size_t tile = (size_t)NG * gt_stride(shape);
-    size_t red = (size_t)NG * TILE + (size_t)waves * NG * ne;
-    size_t gslot = tile > red ? tile : red;
-    const size_t dpg = (size_t)waves * max_dpw;
-    // grid slot, edge buffers, phi table, (r, delta) table
-    return (gslot + dpg * 9 * ne + dpg * 2) * sizeof(double) + dpg * 2 * sizeof(int);
+    const int ne = n_edges(shape);
+    const size_t gslot = std::max(NG * gt_stride(shape), red_doubles(waves, ne));
+    return (nslot * gslot + dir_doubles(waves, max_dpw, ne)) * sizeof(double);
 }
 
 template <int SH, bool NT, int RK>
@@ -1212,12 +816,11 @@ static hipError_t launch_stage1d_sh(int mode, const WorkItem *work, int nwork, c
                                     int waves, int max_dpw, hipStream_t s)
 {
     const dim3 grid(nwork), block(waves * TILE);
-    size_t smem = stage1d_smem_bytes(waves, max_dpw, SH);
     // staged tiles of earlier stages' grids (k1: stages 2 and 4, and 3 when
     // k2 is formed too; k2: stages 3 and 4)
     const int ntiles = ((RK >= 1 && (mode == M_S2 || mode == M_S4)) || (RK >= 2 && mode == M_S3) ? 1 : 0) +
                        (RK >= 2 && (mode == M_S3 || mode == M_S4) ? 1 : 0);
-    smem += sizeof(double) * NG * gt_stride(SH + 1) * ntiles;
+    const size_t smem = smem1d_bytes(waves, max_dpw, SH, 1) + sizeof(double) * NG * gt_stride(SH + 1) * ntiles;
     switch (mode) {
     case M_S1: stage1d_kernel<M_S1, SH, NT, RK><<<grid, block, smem, s>>>(work, sims, max_dpw); break;
     case M_S2: stage1d_kernel<M_S2, SH, NT, RK><<<grid, block, smem, s>>>(work, sims, max_dpw); break;
@@ -1264,16 +867,6 @@ hipError_t launch_reduce1d(const RedItem *items, int nitems, const SimDesc *sims
     return hipGetLastError();
 }
 
-size_t adj1d_smem_bytes(int waves, int max_dpw, int shape)
-{
-    const size_t ne = n_edges(shape);
-    size_t tile = (size_t)NG * gt_stride(shape);
-    size_t red = (size_t)NG * TILE + (size_t)waves * NG * ne;
-    size_t gslot = tile > red ? tile : red;
-    const size_t dpg = (size_t)waves * max_dpw;
-    return (2 * gslot + dpg * 9 * ne + dpg * 2) * sizeof(double) + dpg * 2 * sizeof(int);
-}
-
 // kind 4: stage 4 sources; 3, 2, 1: gather of stage kind+1 fused with the
 // sources of stage kind; 0: gather of stage 1
 template <int SH>
@@ -1281,7 +874,7 @@ static hipError_t launch_adj1d_sh(int kind, const WorkItem *work, int nwork, con
                                   int waves, int max_dpw, hipStream_t s)
 {
     const dim3 grid(nwork), block(waves * TILE);
-    const size_t smem = adj1d_smem_bytes(waves, max_dpw, SH);
+    const size_t smem = smem1d_bytes(waves, max_dpw, SH, 2);
     switch (kind) {
     case 4: adj1d_kernel<false, true, 5, 4, SH><<<grid, block, smem, s>>>(work, sims, max_dpw); break;
     case 3: adj1d_kernel<true, true, 4, 3, SH><<<grid, block, smem, s>>>(work, sims, max_dpw); break;

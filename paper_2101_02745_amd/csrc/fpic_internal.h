@@ -78,6 +78,9 @@ struct SimDesc {
     double *G[5];
     double *part;                // [ngroup][36][ntile*TILE] per-group partials
     double *edge;                // [ngroup][36][n_edges][ntile] edge partials
+    // whole steps in one launch: the partials of every other stage
+    // and [2][ndir][ntile][54] particles that pass to the next tile
+    double *part2, *edge2, *xch;
     double *red;                 // [nred][18] scratch for reductions
     int64_t *step;               // current step number
     // adjoint (reverse-mode) buffers, null outside the adjoint
@@ -108,6 +111,33 @@ hipError_t launch_stage1d(int mode, const WorkItem *work, int nwork, const SimDe
                           hipStream_t s);
 hipError_t launch_reduce1d(const RedItem *items, int nitems, const SimDesc *sims, int which,
                            double *override_out, int tick, hipStream_t s);
+// Grid barriers of the kernels that run whole steps (fpic_1d_steps.hip).
+// cnt: zeroed counters in the workspace that only these kernels write: one
+// per 16 workgroups and one over those, the arrivals, and the decision
+// whether a launch's workgroups run together.  launch, gen: launches and
+// barriers so far (every launch has a known number, so that the counters are
+// never cleared).  arrive_ticks: how long (in 10 ns) a workgroup waits for
+// the others to be resident.  failed: set (host memory) if a resident
+// workgroup then waits longer at a barrier than any step can take, after
+// which no result of the context is valid.
+constexpr int kBarStride = 64, kBarGroup = 16, kMaxStepWgs = 256, kMinStepCells = 16;
+constexpr int kBarArrive = kBarStride * (1 + kMaxStepWgs / kBarGroup), kBarMode = kBarArrive + kBarStride;
+constexpr int kBarWords = kBarMode + kBarStride;
+struct GridBar {
+    unsigned *cnt;
+    unsigned launch, gen;
+    unsigned long long arrive_ticks;
+    int *failed;
+};
+// nsteps steps of every box (4 nsteps barriers) in one launch of one
+// workgroup per work item, one direction per wave; step j uses the
+// descriptors sims + j stride.  keep: the grids and slopes of every stage go
+// to G and K1..K3 (for the adjoint), else only the next stage-1 grid.  No two
+// such launches may run at the same time on a device.  steps1d_fits: whether
+// all workgroups fit the current device at once.
+bool steps1d_fits(int nwork, int waves, int shape);
+hipError_t launch_steps1d(const WorkItem *work, int nwork, const SimDesc *sims, int stride, int keep,
+                          int waves, int shape, int nsteps, const GridBar &bar, hipStream_t s);
 // adjoint kernels: kind 4 = sources of stage 4 and their deposit; kind 3, 2,
 // 1 = gather of the sources of stage kind+1 (stage lambda, step lambda,
 // weight gradients) fused with the sources of stage kind; kind 0 = gather of
@@ -124,7 +154,7 @@ hipError_t launch_totals(const SimDesc *sims, int sim, int nblk, double *out18, 
 hipError_t launch_check(const SimDesc *sims, int sim, int nblk, double *out2, hipStream_t s);
 hipError_t launch_fill_state(const SimDesc *sims, int sim, hipStream_t s);
 
-size_t stage1d_smem_bytes(int waves, int max_dpw, int shape);
+int set_arrive_ticks(void *ctx, unsigned long long ticks);
 
 // Record msg as the calling thread's last error and return code.
 int fail(int code, const std::string &msg);

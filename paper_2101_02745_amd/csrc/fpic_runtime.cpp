@@ -56,13 +56,25 @@ struct Carver {
 };
 
 constexpr int kRedBlocks = 256;  // blocks of the diagnostic reductions
+constexpr int kFailed = 63;      // word of the pinned buffer: a step launch failed
+// Contexts whose waves have one direction each, in at most one workgroup per
+// CU, run whole steps in one launch (fpic_1d_steps.hip), if a tile has at most
+// kMaxStepGroups direction groups: every workgroup sums all groups' partials
+// of its tile in every stage.  us per step, one launch per stage and
+// reduction (the faster slope form) against whole steps: 32 cells x 26
+// directions 66 -> 38, 200 x 92 (12 groups) 81 -> 57, 777 x 92 quadratic (12)
+// 108 -> 76, 512 x 128 (16) 79 -> 65, 2048 x 64 (8) 87 -> 67; but 256 x 378
+// (48) 95 -> 103.
+constexpr int64_t kMaxStepParticles = (int64_t)kMaxStepWgs * MAX_WAVES * TILE;
+constexpr int kMaxStepGroups = 24;
+constexpr int kStepsPerLaunch = 512;
 
 // Sizes and offsets of one simulation inside the workspace.
 struct SimPlan {
     int ncell = 0, ndir = 0, ntile = 0, ngroup = 0, dpw = 0;
     int64_t np = 0;
     size_t o_tab = 0, o_Y = 0, o_K1 = 0, o_K2 = 0, o_K3 = 0, o_G0 = 0, o_G1 = 0, o_G2 = 0, o_G3 = 0;
-    size_t o_part = 0, o_edge = 0, o_step = 0;
+    size_t o_part = 0, o_edge = 0, o_part2 = 0, o_edge2 = 0, o_step = 0;
 };
 
 struct Plan {
@@ -70,8 +82,9 @@ struct Plan {
     bool nt = false;  // streaming cache policy in the stage kernels
     int rk = 2;       // slopes formed again: 2 k1 and k2, 1 k1, 0 none
     std::vector<SimPlan> sims;
-    size_t o_desc = 0, o_work = 0, o_red = 0, o_scratch = 0, total = 0;
+    size_t o_desc = 0, o_work = 0, o_red = 0, o_scratch = 0, o_bar = 0, total = 0;
     int nwork = 0, nred = 0;
+    bool steps = false;  // small enough for whole steps in one launch
 };
 
 int validate_1d(const fpic_config &c, int idx)
@@ -234,13 +247,31 @@ int make_plan(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, Plan &
     const int fused = tune ? tune->fused : 0;
     if (fused < 0 || fused > 2)
         return fail(FPIC_EINVAL, "fused must be 0, 1 or 2");
-    P.rk = 2 - fused;
     int dpw = (tune && tune->dirs_per_wave) ? tune->dirs_per_wave : 0;
     if (dpw < 0 || dpw > 256)
         return fail(FPIC_EINVAL, "dirs_per_wave must be in 0..256");
     choose_shape(nsim, cfgs, P.waves, dpw);
-    Carver cv;
+    // Slopes formed again pay where a stage is bound by its memory traffic.
+    // With one direction a wave it is bound by latency, and storing them is
+    // faster (us per step: 256 x 378 94.6 against 97.9, 2048 x 64 87 against
+    // 91, 32 x 26 66 against 76); the results are the same bits.
+    P.rk = fused == 0 && dpw == 1 ? 0 : 2 - fused;
     P.sims.resize(nsim);
+    int64_t nwork = 0, np_all = 0;
+    int nc_min = INT32_MAX, ng_max = 0;
+    for (int i = 0; i < nsim; ++i) {
+        const int64_t dpg = (int64_t)P.waves * std::min(dpw, cfgs[i].ndir);
+        const int ng = (int)((cfgs[i].ndir + dpg - 1) / dpg);
+        nwork += (int64_t)((cfgs[i].ncell[2] + TILE - 1) / TILE) * ng;
+        ng_max = std::max(ng_max, ng);
+        np_all += (int64_t)cfgs[i].ncell[2] * cfgs[i].ndir;
+        nc_min = std::min(nc_min, cfgs[i].ncell[2]);
+    }
+    // (room for every launch shape of a small box, so that a shape tried in
+    // the workspace of another one fits)
+    const bool small = !external_state && fused == 0 && np_all <= kMaxStepParticles && nc_min >= kMinStepCells;
+    P.steps = small && dpw == 1 && nwork <= kMaxStepWgs && ng_max <= kMaxStepGroups;
+    Carver cv;
     for (int i = 0; i < nsim; ++i) {
         SimPlan &s = P.sims[i];
         s.ncell = cfgs[i].ncell[2];
@@ -264,6 +295,8 @@ int make_plan(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, Plan &
         s.o_G3 = cv.take(sizeof(double) * NG * s.ncell);
         s.o_part = cv.take(sizeof(double) * (size_t)s.ngroup * NG * s.ntile * TILE);
         s.o_edge = cv.take(sizeof(double) * (size_t)s.ngroup * NG * n_edges(P.shape) * s.ntile);
+        s.o_part2 = cv.take(small ? sizeof(double) * (size_t)s.ngroup * NG * s.ntile * TILE : 0);
+        s.o_edge2 = cv.take(small ? sizeof(double) * (size_t)s.ngroup * NG * n_edges(P.shape) * s.ntile : 0);
         s.o_step = cv.take(sizeof(int64_t));
         P.nwork += s.ntile * s.ngroup;
         P.nred += s.ntile;
@@ -273,6 +306,7 @@ int make_plan(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, Plan &
     P.o_work = cv.take(sizeof(WorkItem) * 2 * (size_t)P.nwork);
     P.o_red = cv.take(sizeof(RedItem) * (size_t)P.nred);
     P.o_scratch = cv.take(sizeof(double) * (3 + 18 + 18 * kRedBlocks + 3 * kRedBlocks));
+    P.o_bar = cv.take(small ? sizeof(unsigned) * kBarWords : 0);
     P.total = align_up(cv.off);
     return FPIC_OK;
 }
@@ -293,6 +327,13 @@ struct fpic_batch {
     std::vector<int> swork_off, sred_off;
     std::vector<bool> state_set;
     hipGraphExec_t g1 = nullptr, gK = nullptr;
+    bool steps = false;            // whole steps in one launch (fpic_1d_steps.hip)
+    unsigned launches = 0, gen = 0;  // such launches, and their grid barriers, so far
+    hipEvent_t done = nullptr;     // after the latest such launch
+    // how long its workgroups wait to be resident together before one of them
+    // does all the work (in ticks of 10 ns; 1 s)
+    unsigned long long arrive_ticks = 100000000ull;
+    int device = 0;
     double cell_volume = 1.0;      // of simulation 0
     // reverse mode (single 1D box)
     struct Adj {
@@ -338,6 +379,64 @@ int capture_steps(fpic_batch *b, int nsteps, hipGraphExec_t *exec)
     HIPCHECK(e3);
     return FPIC_OK;
 }
+
+// The step graphs; a context that runs whole steps in one launch captures
+// them only if it is stepped while its stream is being captured.
+int ensure_graphs(fpic_batch *b)
+{
+    int rc = b->g1 ? FPIC_OK : capture_steps(b, 1, &b->g1);
+    if (!rc && b->plan.spg > 1 && !b->gK)
+        rc = capture_steps(b, b->plan.spg, &b->gK);
+    return rc;
+}
+
+// Whether a launch of whole steps gave up a wait (see GridBar).
+int steps_ok(const fpic_batch *b)
+{
+    int failed;
+    std::memcpy(&failed, b->hbuf + kFailed, sizeof failed);
+    return failed ? fail(FPIC_EHIP, "the workgroups of a step launch did not run together") : FPIC_OK;
+}
+
+// The latest launch of whole steps on each device.  The workgroups of such a
+// launch wait for one another, so two of them must not hold parts of the chip
+// at the same time: a launch waits for the latest one of another context.
+constexpr int kMaxStepDevices = 64;
+std::mutex g_steps_mu;
+fpic_batch *g_steps_last[kMaxStepDevices];
+
+// nsteps steps of the descriptors ds + j stride in one launch.
+int run_steps(fpic_batch *b, const SimDesc *ds, int stride, int keep, int nsteps)
+{
+    const Plan &P = b->plan;
+    const GridBar bar{reinterpret_cast<unsigned *>(b->ws + P.o_bar), b->launches, b->gen, b->arrive_ticks,
+                      reinterpret_cast<int *>(b->hbuf + kFailed)};
+    std::lock_guard<std::mutex> lock(g_steps_mu);
+    fpic_batch *&last = g_steps_last[b->device];
+    if (last && last != b)
+        HIPCHECK(hipStreamWaitEvent(b->stream, last->done, 0));
+    HIPCHECK(launch_steps1d(b->dwork, P.nwork, ds, stride, keep, P.waves, P.shape, nsteps, bar, b->stream));
+    b->launches += 1u;
+    b->gen += 4u * (unsigned)nsteps;
+    last = b;
+    HIPCHECK(hipEventRecord(b->done, b->stream));
+    return FPIC_OK;
+}
+
+}  // namespace
+
+// For tests: how long the workgroups of this context's step launches wait for
+// one another (0: one workgroup does all the work).
+int fpic::set_arrive_ticks(void *ctx, unsigned long long ticks)
+{
+    fpic_ctx *c = static_cast<fpic_ctx *>(ctx);
+    if (!c || !c->b || !c->b->steps)
+        return fail(FPIC_EINVAL, "not a context that runs whole steps in one launch");
+    c->b->arrive_ticks = ticks;
+    return FPIC_OK;
+}
+
+namespace {
 
 // The dispatcher hands workgroup b to XCD b % 8, and each XCD has its own
 // L2.  Place item i of the preferred sequence at launch slot b such that
@@ -449,6 +548,11 @@ void build_tables(const Plan &P, const fpic_config *cfgs, char *ws, HostTables &
         D.G[4] = g0;
         D.part = reinterpret_cast<double *>(ws + s.o_part);
         D.edge = reinterpret_cast<double *>(ws + s.o_edge);
+        D.part2 = reinterpret_cast<double *>(ws + s.o_part2);
+        D.edge2 = reinterpret_cast<double *>(ws + s.o_edge2);
+        // (launches of whole steps store no slope in the context's own
+        // buffers; with two tiles or more, 16 ndir ncell > 108 ndir ntile)
+        D.xch = D.K1;
         D.red = reinterpret_cast<double *>(ws + P.o_scratch);
         D.step = reinterpret_cast<int64_t *>(ws + s.o_step);
 
@@ -556,11 +660,20 @@ int batch_build(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, void
     if (e != hipSuccess)
         return cleanup(fail(FPIC_EHIP, std::string("create: ") + hipGetErrorString(e)));
 
-    rc = capture_steps(b, 1, &b->g1);
-    if (!rc && P.spg > 1)
-        rc = capture_steps(b, P.spg, &b->gK);
-    if (rc)
-        return cleanup(rc);
+    b->hbuf[kFailed] = 0.0;
+    b->steps = P.steps && hipGetDevice(&b->device) == hipSuccess && b->device < kMaxStepDevices &&
+               steps1d_fits(P.nwork, P.waves, P.shape);
+    if (b->steps) {
+        e = hipMemset(b->ws + P.o_bar, 0, sizeof(unsigned) * kBarWords);
+        if (e == hipSuccess)
+            e = hipEventCreateWithFlags(&b->done, hipEventDisableTiming);
+        if (e != hipSuccess)
+            return cleanup(fail(FPIC_EHIP, std::string("create: ") + hipGetErrorString(e)));
+    } else {
+        rc = ensure_graphs(b);
+        if (rc)
+            return cleanup(rc);
+    }
     *out = b;
     return FPIC_OK;
 }
@@ -601,6 +714,24 @@ int batch_step(fpic_batch *b, int64_t nsteps)
             return fail(FPIC_ESTATE, "step before set_state");
     const int K = b->plan.spg;
     int64_t left = nsteps;
+    if (b->steps) {
+        int rc = steps_ok(b);
+        if (rc)
+            return rc;
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (left > 0 && hipStreamIsCapturing(b->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
+            for (; left > 0; left -= kStepsPerLaunch) {
+                rc = run_steps(b, b->ddesc, 0, 0, (int)std::min<int64_t>(left, kStepsPerLaunch));
+                if (rc)
+                    return rc;
+            }
+            return FPIC_OK;
+        }
+        (void)hipGetLastError();
+        rc = ensure_graphs(b);
+        if (rc)
+            return rc;
+    }
     while (K > 1 && left >= K) {
         HIPCHECK(hipGraphLaunch(b->gK, b->stream));
         left -= K;
@@ -620,7 +751,7 @@ int batch_totals(fpic_batch *b, int sim, double *out18)
     HIPCHECK(hipMemcpyAsync(b->hbuf, b->dscratch, sizeof(double) * 18, hipMemcpyDeviceToHost, b->stream));
     HIPCHECK(hipStreamSynchronize(b->stream));
     std::memcpy(out18, b->hbuf, sizeof(double) * 18);
-    return FPIC_OK;
+    return steps_ok(b);
 }
 
 }  // namespace
@@ -682,7 +813,7 @@ int fpic_batch_sync(fpic_batch *b)
     if (!b)
         return fail(FPIC_EINVAL, "null batch");
     HIPCHECK(hipStreamSynchronize(b->stream));
-    return FPIC_OK;
+    return steps_ok(b);
 }
 
 void fpic_batch_destroy(fpic_batch *b)
@@ -695,6 +826,15 @@ void fpic_batch_destroy(fpic_batch *b)
         (void)hipGraphExecDestroy(g.second);
     for (auto &g : b->adj.reverse)
         (void)hipGraphExecDestroy(g.second);
+    if (b->steps) {
+        std::lock_guard<std::mutex> lock(g_steps_mu);
+        if (g_steps_last[b->device] == b) {
+            (void)hipEventSynchronize(b->done);
+            g_steps_last[b->device] = nullptr;
+        }
+    }
+    if (b->done)
+        (void)hipEventDestroy(b->done);
     if (b->g1)
         (void)hipGraphExecDestroy(b->g1);
     if (b->gK)
@@ -812,6 +952,9 @@ int fpic_check(fpic_ctx *c, double tol, double *max_trace_err)
         HIPCHECK(hipMemcpyAsync(b->hbuf, b->dscratch, sizeof(double) * 3, hipMemcpyDeviceToHost, b->stream));
         HIPCHECK(hipStreamSynchronize(b->stream));
         std::memcpy(r, b->hbuf, sizeof r);
+        int rc = steps_ok(b);
+        if (rc)
+            return rc;
     }
     const double e = std::max(r[0], r[1]);
     if (max_trace_err)
@@ -860,7 +1003,7 @@ int fpic_get_step(fpic_ctx *c, int64_t *step)
     HIPCHECK(hipMemcpyAsync(b->hbuf, b->hdesc[0].step, sizeof(int64_t), hipMemcpyDeviceToHost, b->stream));
     HIPCHECK(hipStreamSynchronize(b->stream));
     std::memcpy(step, b->hbuf, sizeof(int64_t));
-    return FPIC_OK;
+    return steps_ok(b);
 }
 
 int fpic_sync(fpic_ctx *c)
@@ -1054,7 +1197,7 @@ int read_step(fpic_batch *b, int64_t *step)
     HIPCHECK(hipMemcpyAsync(b->hbuf, b->hdesc[0].step, sizeof(int64_t), hipMemcpyDeviceToHost, b->stream));
     HIPCHECK(hipStreamSynchronize(b->stream));
     std::memcpy(step, b->hbuf, sizeof(int64_t));
-    return FPIC_OK;
+    return steps_ok(b);
 }
 
 }  // namespace
@@ -1186,10 +1329,11 @@ int fpic_adjoint_backward(fpic_ctx *c, const double *dLdy_end, double *dLdy0, do
         HIPCHECK(launch_stage1d(M_DEPOSIT, b->dwork + off, n, F, P.waves, P.max_dpw, P.shape, P.nt, 0, s));
         HIPCHECK(launch_reduce1d(b->dred + roff, rn, F, 0, nullptr, 0, s));
         hipGraphExec_t g = nullptr;
-        int rc = adj_graph(b, false, len, &g);
+        int rc = b->steps ? run_steps(b, F, 1, 1, len) : adj_graph(b, false, len, &g);
         if (rc)
             return rc;
-        HIPCHECK(hipGraphLaunch(g, s));
+        if (!b->steps)
+            HIPCHECK(hipGraphLaunch(g, s));
         // sweep the segment backwards
         HIPCHECK(launch_set_step(F, 0, 1, n0 + len - 1, s));
         rc = adj_graph(b, true, len, &g);
@@ -1207,6 +1351,9 @@ int fpic_adjoint_backward(fpic_ctx *c, const double *dLdy_end, double *dLdy0, do
     // restore the step counter of the context (its state was never touched)
     HIPCHECK(launch_set_step(b->ddesc, 0, 1, n_end, s));
     HIPCHECK(hipStreamSynchronize(s));
+    int rc = steps_ok(b);
+    if (rc)
+        return rc;
     const double inv_dV = 1.0 / b->cell_volume;
     for (int d = 0; d < sp.ndir; ++d) {
         dLdN[d] = h[d] * inv_dV;
