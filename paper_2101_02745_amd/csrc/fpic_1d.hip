@@ -33,6 +33,7 @@
 #include <algorithm>
 
 #include "fpic_1d_body.h"
+#include "fpic_1d_steps.h"
 
 namespace fpic {
 

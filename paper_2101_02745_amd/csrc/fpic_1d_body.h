@@ -1,5 +1,5 @@
 // Device code shared by the 1D kernels (fpic_1d.hip: one launch per stage;
-// fpic_1d_steps.hip: whole steps in one launch): positions, lane moves, the
+// fpic_1d_steps.h: whole steps in one launch): positions, lane moves, the
 // slope path, the deposit of one direction and the sums over a workgroup's
 // waves and over the direction groups.  The arithmetic stands here once, so
 // that both forms round alike, bit for bit.

@@ -1,5 +1,5 @@
 // Whole 1D steps in one launch, for boxes (and batches) of at most one
-// workgroup per CU.
+// workgroup per CU (part of fpic_1d.hip).
 //
 // With one launch per stage and one per reduction, a step of a small box is
 // eight launches of 5 to 27 us each that move almost no data: every launch
@@ -25,6 +25,8 @@
 //
 // Step times (us, one launch per stage -> whole steps): see the rule in
 // fpic_runtime.cpp.
+#pragma once
+
 #include "fpic_1d_body.h"
 
 namespace fpic {

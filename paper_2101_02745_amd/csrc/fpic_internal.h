@@ -111,7 +111,7 @@ hipError_t launch_stage1d(int mode, const WorkItem *work, int nwork, const SimDe
                           hipStream_t s);
 hipError_t launch_reduce1d(const RedItem *items, int nitems, const SimDesc *sims, int which,
                            double *override_out, int tick, hipStream_t s);
-// Grid barriers of the kernels that run whole steps (fpic_1d_steps.hip).
+// Grid barriers of the kernels that run whole steps (fpic_1d_steps.h).
 // cnt: zeroed counters in the workspace that only these kernels write: one
 // per 16 workgroups and one over those, the arrivals, and the decision
 // whether a launch's workgroups run together.  launch, gen: launches and

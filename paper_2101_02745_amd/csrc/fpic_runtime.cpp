@@ -58,7 +58,7 @@ struct Carver {
 constexpr int kRedBlocks = 256;  // blocks of the diagnostic reductions
 constexpr int kFailed = 63;      // word of the pinned buffer: a step launch failed
 // Contexts whose waves have one direction each, in at most one workgroup per
-// CU, run whole steps in one launch (fpic_1d_steps.hip), if a tile has at most
+// CU, run whole steps in one launch (fpic_1d_steps.h), if a tile has at most
 // kMaxStepGroups direction groups: every workgroup sums all groups' partials
 // of its tile in every stage.  us per step, one launch per stage and
 // reduction (the faster slope form) against whole steps: 32 cells x 26
@@ -267,10 +267,10 @@ int make_plan(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, Plan &
         np_all += (int64_t)cfgs[i].ncell[2] * cfgs[i].ndir;
         nc_min = std::min(nc_min, cfgs[i].ncell[2]);
     }
-    // (room for every launch shape of a small box, so that a shape tried in
-    // the workspace of another one fits)
-    const bool small = !external_state && fused == 0 && np_all <= kMaxStepParticles && nc_min >= kMinStepCells;
-    P.steps = small && dpw == 1 && nwork <= kMaxStepWgs && ng_max <= kMaxStepGroups;
+    // (room for every launch shape and slope form of a small box, so that one
+    // tried in the workspace of another fits)
+    const bool small = !external_state && np_all <= kMaxStepParticles && nc_min >= kMinStepCells;
+    P.steps = small && fused == 0 && dpw == 1 && nwork <= kMaxStepWgs && ng_max <= kMaxStepGroups;
     Carver cv;
     for (int i = 0; i < nsim; ++i) {
         SimPlan &s = P.sims[i];
@@ -327,7 +327,7 @@ struct fpic_batch {
     std::vector<int> swork_off, sred_off;
     std::vector<bool> state_set;
     hipGraphExec_t g1 = nullptr, gK = nullptr;
-    bool steps = false;            // whole steps in one launch (fpic_1d_steps.hip)
+    bool steps = false;            // whole steps in one launch (fpic_1d_steps.h)
     unsigned launches = 0, gen = 0;  // such launches, and their grid barriers, so far
     hipEvent_t done = nullptr;     // after the latest such launch
     // how long its workgroups wait to be resident together before one of them
