@@ -18,17 +18,15 @@
 // Hbar (eq. potentials, Sec. II.A conventions), the commutator slopes
 // (eq. eom) and the next stage state, and deposits that state with the
 // next-stage weights (eq. pic_deposition).  Because the particles are sorted
-// by cell, a workgroup's particles cover a small box of cells: it
-// accumulates their deposits in LDS over that box and adds the box into the
-// grid with global atomics.  A workgroup whose box does not fit its LDS
-// (particles spread out) adds straight to the grid.
+// by cell, a workgroup's particles cover a few cells: it sums the particles
+// of a cell in registers and the cells in LDS, and adds those into the grid
+// with global atomics (deposit_runs).
 //
 // Deposits are summed exactly, in integers: each contribution v is scaled
 // by 2^S (S fixed per box from the particle count and the largest weight,
 // so that no contribution and no cell's sum can pass 2^81) and split into
-// two 64-bit limbs,
-// hi = floor(V / 2^32) and lo = V - 2^32 hi in [0, 2^32), V = rint(v 2^S).
-// Integer atomics add the
+// two 64-bit limbs, V = rint(v 2^S) = 2^32 hi + lo, hi the integer nearest to
+// V / 2^32.  Integer atomics add the
 // limbs; integer addition is associative, so the sums do not depend on the
 // order in which the atomics land or on the order of the particles within
 // a cell (the counting sort leaves that order to its atomics): every run
@@ -68,13 +66,15 @@ using fpic::store_slope;
 
 constexpr int NG = 36;
 constexpr int NXT = 8;   // traceless source components (stage grids: 4 NXT)
+constexpr int NGT = 4 * NXT;
 constexpr int BLK = 256;            // particles (threads) per workgroup
 constexpr int NWAVE = BLK / 64;
-// LDS of the deposit box accumulators: 48 KB with floating-point atomics
-// (three workgroups per CU when the stage kernel needs at most 168 VGPRs),
-// 64 KB for the exact sums, whose limbs take twice the room
-template <bool EXACT>
-constexpr int acc_words() { return EXACT ? 8192 : 6144; }
+// LDS of a stage workgroup (8-byte words): the grid cells it interpolates
+// from, then the particle records and box accumulators of its deposit.  Two
+// workgroups of a 3D box fit a CU (its stage kernels need more than 168
+// registers a lane), three of a 1D box.
+template <bool D3, bool EXACT>
+constexpr int acc_words() { return D3 ? (EXACT ? 9952 : 8192) : (EXACT ? 6400 : 6144); }
 constexpr int MAX_COPIES = 32;      // replicas of the box accumulator
 constexpr int kRedBlk = 256;        // blocks of the diagnostic reductions
 // scratch (8-byte words): [0, 32) results, then the totals partials
@@ -98,12 +98,19 @@ struct PDesc {
     double *pos2, *v2, *wN2, *wNb2, *Y2;
     int32_t *pid2;
     double *K1, *K2, *K3;
-    double *G0, *G1, *G2;
+    double *G0, *G1, *G2;  // [ncell][4 NXT] stage grids
     int64_t *step;
     int32_t *cnt, *cur;  // [ncell] sort counters
-    long long *GL;       // [2][NG][ncell] deposit limbs: hi plane, then lo plane
+    long long *GL;       // deposit limbs: per cell the hi limbs of its components, then the lo limbs
     double qs, qi;       // 2^S and 2^-S: the fixed-point scale of the deposits
 };
+
+// 16-byte global loads
+typedef double double2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double2v gld2(const double *p)
+{
+    return *(const __attribute__((address_space(1))) double2v *)p;
+}
 
 // ---- exact deposit sums -------------------------------------------------
 // v 2^S as the limb pair (hi, lo) with rint(v 2^S) = 2^32 hi + lo and
@@ -123,7 +130,7 @@ __device__ __forceinline__ void to_limbs(double v, double qs, long long &hi, lon
     lo = (long long)(unsigned)__double2loint(r + 0x1p52);
 }
 
-// the double nearest to 2^-S (2^32 a1 + a0) for limb sums a1, a0 (a0 >= 0)
+// the double nearest to 2^-S (2^32 a1 + a0) for limb sums a1, a0
 __device__ __forceinline__ double from_limbs(long long a1, long long a0, double qi)
 {
 #pragma clang fp contract(off)
@@ -141,21 +148,45 @@ __device__ __forceinline__ void gatomic_add_ll(long long *p, long long v)
     __hip_atomic_fetch_add((glong *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void lds_add_limbs(long long *hi_p, long long *lo_p, double v, double qs)
+// The limbs of a deposit contribution w u (stencil weight times source, the
+// source scaled by 2^S): V = rint(w u) = 2^32 hi + lo, |lo| <= 2^31, for
+// |w u| < 2^83.  Adding 1.5 2^84 rounds w u to a multiple of 2^32, whose
+// quotient then stands in the sum's mantissa; what is left of w u (one more
+// fused multiply-add) is rounded to an integer in the same way.  The bits of
+// the two sums are hi and lo plus the bits of the added constants, whose low
+// words are zero.
+constexpr double kLimb1 = 0x1.8p84, kLimb2 = 0x1.8p52;
+constexpr unsigned kBias1 = 0x45380000u, kBias2 = 0x43380000u;  // their high words
+__device__ __forceinline__ void biased_limbs(double w, double u, unsigned long long &hi, unsigned long long &lo)
 {
-    long long hi, lo;
-    to_limbs(v, qs, hi, lo);
-    atomicAdd(reinterpret_cast<unsigned long long *>(hi_p), (unsigned long long)hi);
-    atomicAdd(reinterpret_cast<unsigned long long *>(lo_p), (unsigned long long)lo);
+#pragma clang fp contract(off)
+    const double t = fma(w, u, kLimb1);
+    const double r = fma(w, u, -(t - kLimb1));
+    hi = (unsigned long long)__double_as_longlong(t);
+    lo = (unsigned long long)__double_as_longlong(r + kLimb2);
 }
 
-__device__ __forceinline__ void global_add_limbs(long long *GL, int64_t plane, int64_t q, double v,
-                                                 double qs)
+__device__ __forceinline__ void product_limbs(double w, double u, unsigned long long &hi, unsigned long long &lo)
 {
-    long long hi, lo;
-    to_limbs(v, qs, hi, lo);
-    gatomic_add_ll(GL + q, hi);
-    gatomic_add_ll(GL + plane + q, lo);
+    biased_limbs(w, u, hi, lo);
+    hi -= (unsigned long long)kBias1 << 32;
+    lo -= (unsigned long long)kBias2 << 32;
+}
+
+__device__ __forceinline__ void lds_add_limbs(long long *hi_p, long long *lo_p, double m, double x)
+{
+    unsigned long long hi, lo;
+    product_limbs(m, x, hi, lo);
+    atomicAdd(reinterpret_cast<unsigned long long *>(hi_p), hi);
+    atomicAdd(reinterpret_cast<unsigned long long *>(lo_p), lo);
+}
+
+__device__ __forceinline__ void global_add_limbs(long long *GL, int plane, int64_t q, double m, double x)
+{
+    unsigned long long hi, lo;
+    product_limbs(m, x, hi, lo);
+    gatomic_add_ll(GL + q, (long long)hi);
+    gatomic_add_ll(GL + plane + q, (long long)lo);
 }
 
 // Limb sums of one box entry (LDS offset q of each of the R copies, hi
@@ -298,6 +329,295 @@ __device__ __forceinline__ Box block_box(const int f[3], bool active, const int 
     return b;
 }
 
+// Deposit of a workgroup's particles run by run, a run being its particles of
+// one stencil (the same first cell).  An LDS atomic for every contribution
+// bounds the kernels: a 64-bit one takes about 33 cycles of a CU for a wave,
+// and a particle of a 3D box makes 512 (linear shape).  Here the particles are
+// put in cell order in LDS (a counting sort of their records), each wave takes
+// 64 of them, and its lanes own the components: lane l sums component l % 32
+// over the run's particles l / 32, l / 32 + 2, ... in registers, all stencil
+// corners at once.  At the end of a run the two halves of the wave are added
+// so that its lower half holds the hi limbs and its upper half the lo limbs,
+// and every corner takes one atomic of 64 consecutive words: into the box
+// accumulators in LDS (a slot of 64 words for every cell that any run
+// touches), or, where those do not fit, straight into the grid.  The limbs are
+// the same whatever the way, and integer sums do not depend on the order.
+// Measured per step with exact sums, against one LDS atomic per contribution
+// into replicated boxes: 32^3 cells x 92 particles 5.41 -> 3.33-3.69 ms (stage
+// 2 1.24 -> 0.74 ms), 2048 x 378 470 -> 412 us, 2048 x 378 quadratic 608 ->
+// 446 us, 2048 x 40 107 -> 93 us; with floating-point atomics 4.80 -> 2.84 ms
+// and (unchanged) 384 -> 382 us.  The 3D kernels are now bound by the sums'
+// FP64 and integer instructions (for each of 8 corners two fused multiply-adds,
+// two adds and two 64-bit integer adds per two components); the 1D ones by
+// their particle streams.
+// Returns false (workgroup-uniform) if the first cells of the workgroup's
+// particles spread over more than kMaxLow cells (the counters of the sort, in
+// the place of the accumulators; x, y, z in 12, 10, 10 bits); the caller then
+// adds particle by particle.
+constexpr int kMaxLow = 4096, kMaxSlots = 128, kMaxMap = 1024;
+
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+
+// (a's lower half, b's lower half in the upper lanes) and (a's upper half in
+// the lower lanes, b's upper half), for 64-bit values
+__device__ __forceinline__ void swap_halves(unsigned long long &a, unsigned long long &b)
+{
+    const uint2v l = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+    const uint2v h = __builtin_amdgcn_permlane32_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+    a = ((unsigned long long)h[0] << 32) | l[0];
+    b = ((unsigned long long)h[1] << 32) | l[1];
+}
+
+template <int SH, bool D3, bool EXACT>
+__device__ __forceinline__ bool deposit_runs(const PDesc &S, const Box &db, const int o[3], bool active,
+                                             const double Xd[NXT], const double dw[3][3], double vx,
+                                             double vy, double vz, double *acc, double *G)
+{
+    constexpr int SW = SH + 1, NCORNER = D3 ? SW * SW * SW : SW;
+    constexpr int LW = EXACT ? 64 : 32;  // words of a slot
+    // record: 8 source components, (1, vx, vy, vz), per axis phi (linear) or
+    // the three weights; an odd stride
+    constexpr int NAX = D3 ? 3 : 1, NW = SH == 2 ? 3 : 1;
+    constexpr int NREC = (12 + NAX * NW) | 1;
+    constexpr int MAPW = kMaxMap / 4;    // the slot of every box cell, 16 bits each
+    constexpr int ACCW = acc_words<D3, EXACT>() - NREC * BLK - MAPW;
+    constexpr int NSLOT = ACCW / LW < kMaxSlots ? ACCW / LW : kMaxSlots;
+    static_assert(kMaxLow / 2 <= ACCW, "the counters take the accumulators' place");
+    __shared__ unsigned rpos[BLK];  // a run's first cell in the box: x, y, z in 12, 10, 10 bits
+    __shared__ unsigned short rbeg[BLK + 1], wfirst[NWAVE];
+    __shared__ int wtot[NWAVE][2];
+    __shared__ int slot_cell[NSLOT];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = threadIdx.x;
+    const int sx = db.s[0], sy = db.s[1];
+    const int lx = D3 ? sx - SW + 1 : 1, ly = D3 ? sy - SW + 1 : 1, lz = db.s[2] - SW + 1;
+    if ((int64_t)lx * ly * lz > kMaxLow || ly > 1024 || lz > 1024)
+        return false;
+    const int nlow = lx * ly * lz;
+    const int nx = S.n[0], ny = S.n[1], nz = S.n[2];
+
+    // counting sort by first cell; thread t has the cells [c0, c1)
+    int *hist = reinterpret_cast<int *>(acc);
+    const int ox = D3 ? o[0] - db.lo[0] : 0, oy = D3 ? o[1] - db.lo[1] : 0, oz = o[2] - db.lo[2];
+    const int key = (oz * ly + oy) * lx + ox;
+    const int per = (nlow + BLK - 1) / BLK, c0 = min(t * per, nlow), c1 = min(c0 + per, nlow);
+    for (int c = c0; c < c1; c++)
+        hist[c] = 0;
+    __syncthreads();
+    const int rank = active ? atomicAdd(&hist[key], 1) : 0;
+    __syncthreads();
+    // exclusive sums over the threads of the particles and the used cells
+    auto scan2 = [&](int a, int b, int &ea, int &eb) {
+        int ia = a, ib = b;
+#pragma unroll
+        for (int sh = 1; sh < 64; sh <<= 1) {
+            const int va = __shfl_up(ia, sh, 64), vb = __shfl_up(ib, sh, 64);
+            ia += lane >= sh ? va : 0;
+            ib += lane >= sh ? vb : 0;
+        }
+        if (lane == 63) {
+            wtot[wave][0] = ia;
+            wtot[wave][1] = ib;
+        }
+        __syncthreads();
+        ea = ia - a;
+        eb = ib - b;
+        int ta = 0, tb = 0;
+#pragma unroll
+        for (int w = 0; w < NWAVE; w++) {
+            ea += w < wave ? wtot[w][0] : 0;
+            eb += w < wave ? wtot[w][1] : 0;
+            ta += wtot[w][0];
+            tb += wtot[w][1];
+        }
+        return ta + (tb << 16);
+    };
+    int cnt = 0, used = 0;
+    for (int c = c0; c < c1; c++) {
+        cnt += hist[c];
+        used += hist[c] > 0;
+    }
+    int beg, r;
+    const int tot = scan2(cnt, used, beg, r);
+    const int total = tot & 0xffff, runs = tot >> 16;
+    for (int c = c0; c < c1; c++) {
+        const int n = hist[c];
+        hist[c] = beg;
+        if (n > 0) {
+            rpos[r] = (unsigned)(c % lx) | (unsigned)((c / lx) % ly) << 12 | (unsigned)(c / (lx * ly)) << 22;
+            rbeg[r] = (unsigned short)beg;
+            for (int w = 0; w < NWAVE; w++)  // the run that holds the wave's first particle
+                if (beg <= 64 * w && 64 * w < beg + n)
+                    wfirst[w] = (unsigned short)r;
+            beg += n;
+            if (++r == runs)
+                rbeg[runs] = (unsigned short)beg;
+        }
+    }
+    __syncthreads();
+    const int at_rec = active ? hist[key] + rank : 0;
+    double *rec = acc + ACCW;
+    unsigned short *map = reinterpret_cast<unsigned short *>(acc + ACCW + NREC * BLK);
+    if (active) {
+        double *p = rec + at_rec * NREC;
+#pragma unroll
+        for (int k = 0; k < NXT; k++)
+            p[k] = Xd[k];
+        p[8] = 1.0;
+        p[9] = vx;
+        p[10] = vy;
+        p[11] = vz;
+#pragma unroll
+        for (int a = 0; a < NAX; a++) {
+            const double *w = dw[D3 ? a : 2];
+            if (SH == 2) {
+#pragma unroll
+                for (int q = 0; q < 3; q++)
+                    p[12 + 3 * a + q] = w[q];
+            } else {
+                p[12 + a] = w[1];
+            }
+        }
+    }
+    // a slot for every cell that a run touches
+    bool boxed = db.cells <= kMaxMap;
+    int nslot = 0;
+    if (boxed) {
+        const int cells = (int)db.cells;
+        for (int c = t; c < cells; c += BLK)
+            map[c] = 0;
+        __syncthreads();
+        if (t < runs) {
+            const unsigned q = rpos[t];
+            const int at = (int)(((q >> 22) * sy + ((q >> 12) & 1023u)) * sx + (q & 4095u));
+#pragma unroll
+            for (int c = 0; c < NCORNER; c++)
+                map[at + (D3 ? ((c / (SW * SW)) * sy + (c / SW) % SW) * sx + c % SW : c)] = 1;
+        }
+        __syncthreads();
+        const int pc = (cells + BLK - 1) / BLK, m0 = min(t * pc, cells), m1 = min(m0 + pc, cells);
+        int mine = 0;
+        for (int c = m0; c < m1; c++)
+            mine += map[c];
+        int first, dummy;
+        nslot = scan2(mine, 0, first, dummy) & 0xffff;
+        boxed = nslot <= NSLOT;
+        for (int c = m0; c < m1; c++)
+            if (map[c]) {
+                if (boxed) {
+                    const int cz = wrap_int(db.ref[2] + db.lo[2] + c / (sx * sy), nz);
+                    const int cy = D3 ? wrap_int(db.ref[1] + db.lo[1] + (c / sx) % sy, ny) : 0;
+                    const int cx = D3 ? wrap_int(db.ref[0] + db.lo[0] + c % sx, nx) : 0;
+                    slot_cell[first] = (cz * ny + cy) * nx + cx;
+                }
+                map[c] = (unsigned short)first++;
+            }
+        if (boxed)
+            for (int q = t; q < LW * nslot; q += BLK)
+                acc[q] = 0.0;
+    }
+    __syncthreads();
+
+    const int wbeg = 64 * wave, wend = min(wbeg + 64, total);
+    const int comp = lane & (NGT - 1), par = lane / NGT;
+    boxed = __builtin_amdgcn_readfirstlane((int)boxed) != 0;  // (the same in every lane)
+    const int my_c = min(lane, NCORNER - 1);
+    const int my_dx = D3 ? my_c % SW : 0, my_dy = D3 ? (my_c / SW) % SW : 0, my_dz = D3 ? my_c / (SW * SW) : my_c;
+    const int my_corner = (my_dz * sy + my_dy) * sx + my_dx;
+    const double *rk = rec + (comp & (NXT - 1)), *rm = rec + 8 + comp / NXT;
+    for (int q = wbeg < wend ? (int)wfirst[wave] : runs; q < runs; q++) {
+        const int b = max((int)rbeg[q], wbeg), e = min((int)rbeg[q + 1], wend);
+        if (b >= e)
+            break;
+        // sums of every corner: the limbs' bits, or doubles
+        unsigned long long ah[NCORNER], al[NCORNER];
+        double af[NCORNER];
+#pragma unroll
+        for (int c = 0; c < NCORNER; c++) {
+            ah[c] = al[c] = 0;
+            af[c] = 0.0;
+        }
+        for (int p = b + par; p < e; p += 2) {
+            const double u = rm[p * NREC] * rk[p * NREC];
+            const double *pw = rec + p * NREC + 12;
+            double w[NAX][SW];
+#pragma unroll
+            for (int a = 0; a < NAX; a++) {
+                if (SH == 2) {
+#pragma unroll
+                    for (int i = 0; i < SW; i++)
+                        w[a][i] = pw[3 * a + i];
+                } else {
+                    w[a][0] = 1.0 - pw[a];
+                    w[a][1] = pw[a];
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < NCORNER; c++) {
+                const double wc = D3 ? (w[0][c % SW] * w[NAX - 2][(c / SW) % SW]) * w[NAX - 1][c / (SW * SW)]
+                                     : w[0][c];
+                if (EXACT) {
+                    unsigned long long hi, lo;
+                    biased_limbs(wc, u, hi, lo);
+                    ah[c] += hi;
+                    al[c] += lo;
+                } else {
+                    af[c] += wc * u;
+                }
+            }
+        }
+        // where the corners' sums go, corner c's from lane c
+        const unsigned pos = rpos[q];
+        int dest;
+        if (boxed) {
+            dest = map[(int)(((pos >> 22) * sy + ((pos >> 12) & 1023u)) * sx + (pos & 4095u)) + my_corner];
+        } else {
+            const int cz = wrap_int(db.ref[2] + db.lo[2] + (int)(pos >> 22) + my_dz, nz);
+            const int cy = D3 ? wrap_int(db.ref[1] + db.lo[1] + (int)((pos >> 12) & 1023u) + my_dy, ny) : 0;
+            const int cx = D3 ? wrap_int(db.ref[0] + db.lo[0] + (int)(pos & 4095u) + my_dx, nx) : 0;
+            dest = (cz * ny + cy) * nx + cx;
+        }
+        // the added constants' share in the lower and upper half's sums
+        const unsigned long long bias = (unsigned long long)((unsigned)(e - b) * (par ? kBias2 : kBias1)) << 32;
+#pragma unroll
+        for (int c = 0; c < NCORNER; c++) {
+            const int to = __builtin_amdgcn_readlane(dest, c);
+            if (EXACT) {
+                swap_halves(ah[c], al[c]);
+                const unsigned long long v = ah[c] + al[c] - bias;
+                if (boxed)
+                    atomicAdd(reinterpret_cast<unsigned long long *>(acc) + to * LW + lane, v);
+                else
+                    gatomic_add_ll(S.GL + (int64_t)to * LW + lane, (long long)v);
+            } else {
+                unsigned long long x = (unsigned long long)__double_as_longlong(af[c]), y = x;
+                swap_halves(x, y);
+                const double v = __longlong_as_double((long long)x) + __longlong_as_double((long long)y);
+                if (par == 0) {
+                    if (boxed)
+                        atomicAdd(acc + to * LW + comp, v);
+                    else
+                        gatomic_add(G + (int64_t)to * LW + comp, v);
+                }
+            }
+        }
+    }
+    if (boxed) {
+        __syncthreads();
+        for (int q = t; q < LW * nslot; q += BLK) {
+            const int64_t g = (int64_t)slot_cell[q / LW] * LW + q % LW;
+            if (EXACT) {
+                const long long v = reinterpret_cast<const long long *>(acc)[q];
+                if (v != 0)
+                    gatomic_add_ll(S.GL + g, v);
+            } else {
+                if (acc[q] != 0.0)
+                    gatomic_add(G + g, acc[q]);
+            }
+        }
+    }
+    return true;
+}
+
 // ---- redistribution: counting sort by cell ----------------------------
 // Sort key: the cell whose centre is the nearest one at or below the
 // particle along each axis (the linear stencil's first cell) at the start
@@ -384,8 +704,10 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
     constexpr bool FULL = MODE == PM_MOM_NU || MODE == PM_MOM_NUBAR;
     constexpr int NCS = FULL ? 9 : NXT, NGC = 4 * NCS;
     constexpr int STG = MODE == PM_S4_SORT ? 4 : MODE;  // Runge-Kutta stage
-    constexpr int ACC_DOUBLES = acc_words<EXACT>();
-    __shared__ double acc[ACC_DOUBLES];
+    constexpr int ACC_DOUBLES = acc_words<D3, EXACT>();
+    // LDS words of a staged grid cell: 16-byte aligned, cells four banks apart
+    constexpr int GST = NGT + 2;
+    __shared__ __align__(16) double acc[ACC_DOUBLES];
     __shared__ int sred[NWAVE][6];
     __shared__ int sref[3];
     const PDesc S = *dp;
@@ -435,7 +757,6 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
         for (int64_t q = i; q < len; q += (int64_t)gridDim.x * BLK)
             gst(Gclr + q, 0.0);
     }
-    const int64_t plane = (int64_t)NG * S.ncell;  // hi plane -> lo plane
     const double qs = S.qs;
 
     const double vx = gld(S.v + ip), vy = gld(S.v + np + ip), vz = gld(S.v + 2 * np + ip);
@@ -452,9 +773,7 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
     // particles interpolate from are staged in LDS when they fit, except in
     // stage 4 of a 1D box, which streams the most particle data and reads
     // its two cells per particle through the caches (there the staging
-    // barrier held its streams back).  In 3D the 256 reads per particle
-    // from memory keep only a few loads in flight: staging them took the
-    // random 32^3 box from 6.20 to 5.93 ms per step.
+    // barrier held its streams back).
     int gf[3] = {0, 0, 0}, go[3] = {0, 0, 0};
     double gw[3][3] = {{1.0, 0.0, 0.0}, {1.0, 0.0, 0.0}, {1.0, 0.0, 0.0}};
     Box gb = {};
@@ -468,36 +787,23 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
     }
     if (MODE <= 3 || (D3 && RK)) {
         gb = block_box<SW, D3>(gf, active, nn, sred, sref, go);
-        g_lds = gb.cells * NGC <= ACC_DOUBLES && gb.cells <= BLK;
+        g_lds = gb.cells * GST + gb.cells <= ACC_DOUBLES;
         if (g_lds) {
+            // the grid index of every box cell, then 16 lanes a cell: one
+            // 16-byte piece of its 32 components each
             const int cells = (int)gb.cells;
-            if (D3) {
-                // thread l stages cell l of the box: one cell index
-                // decomposition, all its components' loads in flight at once
-                // (a 3D box has tens of cells; element by element, each
-                // thread's loads waited one after another)
-                const int l = threadIdx.x;
-                if (l < cells) {
-                    const int lx = l % gb.s[0], ly = (l / gb.s[0]) % gb.s[1], lz = l / (gb.s[0] * gb.s[1]);
-                    const int cz = wrap_int(gb.ref[2] + gb.lo[2] + lz, nz);
-                    const int cy = wrap_int(gb.ref[1] + gb.lo[1] + ly, ny);
-                    const int cx = wrap_int(gb.ref[0] + gb.lo[0] + lx, nx);
-                    const double *src = Gin + ((int64_t)cz * ny + cy) * nx + cx;
-                    double v[NGC];
-#pragma unroll
-                    for (int comp = 0; comp < NGC; comp++)
-                        v[comp] = gld(src + (int64_t)comp * nc);
-#pragma unroll
-                    for (int comp = 0; comp < NGC; comp++)
-                        acc[comp * cells + l] = v[comp];
-                }
-            } else {
-                // a 1D box has a few cells: one element per thread
-                for (int q = threadIdx.x; q < NGC * cells; q += BLK) {
-                    const int comp = q / cells, l = q - comp * cells;
-                    const int cz = wrap_int(gb.ref[2] + gb.lo[2] + l, nz);
-                    acc[q] = gld(Gin + (int64_t)comp * nc + cz);
-                }
+            int *gcell = reinterpret_cast<int *>(acc + cells * GST);
+            for (int l = threadIdx.x; l < cells; l += BLK) {
+                const int cz = wrap_int(gb.ref[2] + gb.lo[2] + (D3 ? l / (gb.s[0] * gb.s[1]) : l), nz);
+                const int cy = D3 ? wrap_int(gb.ref[1] + gb.lo[1] + (l / gb.s[0]) % gb.s[1], ny) : 0;
+                const int cx = D3 ? wrap_int(gb.ref[0] + gb.lo[0] + l % gb.s[0], nx) : 0;
+                gcell[l] = (cz * ny + cy) * nx + cx;
+            }
+            __syncthreads();
+#pragma unroll 4
+            for (int q = threadIdx.x; q < cells * (NGT / 2); q += BLK) {
+                const int l = q / (NGT / 2), k = 2 * (q % (NGT / 2));
+                *reinterpret_cast<double2v *>(acc + l * GST + k) = gld2(Gin + (int64_t)gcell[l] * NGT + k);
             }
             __syncthreads();
         }
@@ -531,46 +837,47 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
 #pragma unroll
             for (int k = 0; k < NXT; k++)
                 A[k] = Bx[k] = By[k] = Bz[k] = 0.0;
+            auto add_cell = [&](double w, auto load) {
+#pragma unroll
+                for (int k = 0; k < NXT; k += 2) {
+                    const double2v a = load(k), b = load(NXT + k), c = load(2 * NXT + k), d = load(3 * NXT + k);
+                    A[k] += w * a[0];
+                    A[k + 1] += w * a[1];
+                    Bx[k] += w * b[0];
+                    Bx[k + 1] += w * b[1];
+                    By[k] += w * c[0];
+                    By[k + 1] += w * c[1];
+                    Bz[k] += w * d[0];
+                    Bz[k + 1] += w * d[1];
+                }
+            };
+            // (the rows of a 3D stencil in a rolled loop: unrolled, the loads
+            // of all corners at once would spill)
+            auto add_rows = [&](auto cell_of) {
+#pragma unroll 1
+                for (int row = 0; row < (D3 ? SW * SW : 1); row++) {
+                    const int by = row % SW, bz = row / SW;
+#pragma unroll
+                    for (int b = 0; b < SW; b++) {
+                        const double w = D3 ? (gw[0][b] * pick(gw[1], by)) * pick(gw[2], bz) : gw[2][b];
+                        add_cell(w, cell_of(D3 ? b : 0, by, D3 ? bz : b));
+                    }
+                }
+            };
             if (g_lds) {
-                const int cells = (int)gb.cells;
-#pragma unroll
-                for (int bz = 0; bz < SW; bz++)
-#pragma unroll
-                    for (int by = 0; by < (D3 ? SW : 1); by++)
-#pragma unroll
-                        for (int bx = 0; bx < (D3 ? SW : 1); bx++) {
-                            const double w = D3 ? (gw[0][bx] * gw[1][by]) * gw[2][bz] : gw[2][bz];
-                            const double *g = acc + ((go[2] - gb.lo[2] + bz) * gb.s[1] +
-                                                     (go[1] - gb.lo[1] + by)) * gb.s[0] +
-                                              (go[0] - gb.lo[0] + bx);
-#pragma unroll
-                            for (int k = 0; k < NXT; k++) {
-                                A[k] += w * g[k * cells];
-                                Bx[k] += w * g[(NXT + k) * cells];
-                                By[k] += w * g[(2 * NXT + k) * cells];
-                                Bz[k] += w * g[(3 * NXT + k) * cells];
-                            }
-                        }
+                add_rows([&](int bx, int by, int bz) {
+                    const double *g = acc + (((go[2] - gb.lo[2] + bz) * gb.s[1] + (go[1] - gb.lo[1] + by)) *
+                                                 gb.s[0] + (go[0] - gb.lo[0] + bx)) * GST;
+                    return [g](int k) { return *reinterpret_cast<const double2v *>(g + k); };
+                });
             } else {
-#pragma unroll
-                for (int bz = 0; bz < SW; bz++)
-#pragma unroll
-                    for (int by = 0; by < (D3 ? SW : 1); by++)
-#pragma unroll
-                        for (int bx = 0; bx < (D3 ? SW : 1); bx++) {
-                            const double w = D3 ? (gw[0][bx] * gw[1][by]) * gw[2][bz] : gw[2][bz];
-                            const int cz = wrap_int(gf[2] + bz, nz);
-                            const int cy = D3 ? wrap_int(gf[1] + by, ny) : 0;
-                            const int cx = D3 ? wrap_int(gf[0] + bx, nx) : 0;
-                            const double *g = Gin + ((int64_t)cz * ny + cy) * nx + cx;
-#pragma unroll
-                            for (int k = 0; k < NXT; k++) {
-                                A[k] += w * gld(g + (int64_t)k * nc);
-                                Bx[k] += w * gld(g + (int64_t)(NXT + k) * nc);
-                                By[k] += w * gld(g + (int64_t)(2 * NXT + k) * nc);
-                                Bz[k] += w * gld(g + (int64_t)(3 * NXT + k) * nc);
-                            }
-                        }
+                add_rows([&](int bx, int by, int bz) {
+                    const int cz = wrap_int(gf[2] + bz, nz);
+                    const int cy = D3 ? wrap_int(gf[1] + by, ny) : 0;
+                    const int cx = D3 ? wrap_int(gf[0] + bx, nx) : 0;
+                    const double *g = Gin + (((int64_t)cz * ny + cy) * nx + cx) * NGT;
+                    return [g](int k) { return gld2(g + k); };
+                });
             }
             // traceless Hnn: its ee entry is 0
             double Hnn[9];
@@ -661,6 +968,12 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
         for (int k = 2; k < NCS; k++)
             Xd[k] = X[k + 1];
     }
+    // (exact sums: scaled to the fixed-point unit, a power of two)
+    if (EXACT) {
+#pragma unroll
+        for (int k = 0; k < NCS; k++)
+            Xd[k] *= qs;
+    }
     int df[3] = {0, 0, 0}, o[3];
     double dw[3][3] = {{1.0, 0.0, 0.0}, {1.0, 0.0, 0.0}, {1.0, 0.0, 0.0}};
     axis_stencil<SH>(pz, vz, t_nxt, S.dx[2], nz, &df[2], dw[2]);
@@ -676,8 +989,18 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
     // instruction's lanes target different corners
     const int rot = lane % NCORNER;
 
-    if (EXACT) {
-        // Limb accumulators of the box in LDS: some of the four groups
+    // grid index of the moment kernels' box cell l
+    auto box_cell = [&](int l) {
+        const int cz = wrap_int(db.ref[2] + db.lo[2] + (D3 ? l / (sx * sy) : l), nz);
+        const int cy = D3 ? wrap_int(db.ref[1] + db.lo[1] + (l / sx) % sy, ny) : 0;
+        const int cx = D3 ? wrap_int(db.ref[0] + db.lo[0] + l % sx, nx) : 0;
+        return ((int64_t)cz * ny + cy) * nx + cx;
+    };
+    if (!FULL && deposit_runs<SH, D3, EXACT>(S, db, o, active, Xd, dw, vx, vy, vz, acc, Gout)) {
+        // the stages' deposit
+    } else if (EXACT) {
+        // The moment diagnostics, contribution by contribution.  Limb
+        // accumulators of the box in LDS: some of the four groups
         // (A, B_x, B_y, B_z) per pass, R copies of them (lane l adding into
         // copy (l / NCORNER) % R: lanes of a dense workgroup target the same
         // few cells, and the copies and the corner rotation spread their
@@ -698,7 +1021,7 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
                 break;
             gpp >>= 1;
         }
-        if (R > 0 && box <= ACC_DOUBLES) {
+        if (FULL && R > 0 && box <= ACC_DOUBLES) {
             const int half = NCS * gpp * cells;
             const int cstride = 2 * half + 1;
             long long *lacc = reinterpret_cast<long long *>(acc);
@@ -714,6 +1037,10 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
                     for (int g = 0; g < gpp; g++) {
                         const int gg = g0 + g;
                         const double m = gg == 0 ? 1.0 : (gg == 1 ? vx : (gg == 2 ? vy : vz));
+                        double u[NCS];
+#pragma unroll
+                        for (int k = 0; k < NCS; k++)
+                            u[k] = m * Xd[k];
                         long long *mg = mine + g * NCS * cells;
                         // (a rolled corner loop: unrolled, the limb
                         // conversions of all corners would spill)
@@ -728,42 +1055,19 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
                                                 : pick(dw[2], bz);
                             const int idx = ((o[2] - db.lo[2] + bz) * sy + (o[1] - db.lo[1] + by)) * sx +
                                             (o[0] - db.lo[0] + bx);
+                            long long *a = mg + idx;
 #pragma unroll
-                            for (int k = 0; k < NCS; k++) {
-                                // m * (w X_k): the product the floating-point
-                                // path forms (1 * x is x)
-                                const double xc = w * Xd[k];
-                                long long *a = mg + idx + k * cells;
-                                lds_add_limbs(a, a + half, m * xc, qs);
-                            }
+                            for (int k = 0; k < NCS; k++)
+                                lds_add_limbs(a + k * cells, a + k * cells + half, w, u[k]);
                         }
                     }
                 }
                 __syncthreads();
-                // flush; integer sums, so the order in which the atomics land
-                // does not matter
-                if (D3) {
-                    // BLK / cells threads per box cell (each forms the cell's
-                    // grid index once) share the pass's components
-                    const int per = cells < BLK ? BLK / cells : 1;
-                    for (int t = threadIdx.x; t < per * cells; t += BLK) {
-                        const int l = t % cells, c0 = t / cells;
-                        const int lx = l % sx, ly = (l / sx) % sy, lz = l / (sx * sy);
-                        const int cz = wrap_int(db.ref[2] + db.lo[2] + lz, nz);
-                        const int cy = wrap_int(db.ref[1] + db.lo[1] + ly, ny);
-                        const int cx = wrap_int(db.ref[0] + db.lo[0] + lx, nx);
-                        const int64_t cell = ((int64_t)cz * ny + cy) * nx + cx;
-                        for (int c = c0; c < NCS * gpp; c += per)
-                            flush_limbs(lacc, R, cstride, half, c * cells + l, S.GL,
-                                        (int64_t)(g0 * NCS + c) * nc + cell, plane);
-                    }
-                } else {
-                    // a 1D box has a few cells: one entry per thread
-                    for (int q = threadIdx.x; q < half; q += BLK) {
-                        const int c = q / cells, l = q - c * cells;
-                        const int cz = wrap_int(db.ref[2] + db.lo[2] + l, nz);
-                        flush_limbs(lacc, R, cstride, half, q, S.GL, (int64_t)(g0 * NCS + c) * nc + cz, plane);
-                    }
+                // integer sums, so the order in which the atomics land does
+                // not matter
+                for (int q = threadIdx.x; q < half; q += BLK) {
+                    const int c = q / cells, l = q - c * cells;
+                    flush_limbs(lacc, R, cstride, half, q, S.GL, box_cell(l) * 2 * NGC + g0 * NCS + c, NGC);
                 }
                 __syncthreads();  // the next pass clears the accumulators
             }
@@ -782,15 +1086,14 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
                 const int64_t g = ((int64_t)cz * ny + cy) * nx + cx;
 #pragma unroll 1
                 for (int k = 0; k < NCS; k++) {
-                    const double xc = w * Xd[k];
-                    global_add_limbs(S.GL, plane, g + (int64_t)k * nc, xc, qs);
-                    global_add_limbs(S.GL, plane, g + (int64_t)(NCS + k) * nc, vx * xc, qs);
-                    global_add_limbs(S.GL, plane, g + (int64_t)(2 * NCS + k) * nc, vy * xc, qs);
-                    global_add_limbs(S.GL, plane, g + (int64_t)(3 * NCS + k) * nc, vz * xc, qs);
+                    global_add_limbs(S.GL, NGC, g * 2 * NGC + k, w, Xd[k]);
+                    global_add_limbs(S.GL, NGC, g * 2 * NGC + NCS + k, w, vx * Xd[k]);
+                    global_add_limbs(S.GL, NGC, g * 2 * NGC + 2 * NCS + k, w, vy * Xd[k]);
+                    global_add_limbs(S.GL, NGC, g * 2 * NGC + 3 * NCS + k, w, vz * Xd[k]);
                 }
             }
         }
-    } else if (box * NGC <= ACC_DOUBLES) {
+    } else if (FULL && box * NGC <= ACC_DOUBLES) {
         // floating-point atomics (not reproducible bit for bit): R copies of
         // the box accumulator as above, flushed with global FP64 atomics
         const int cells = (int)box;
@@ -823,33 +1126,13 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
             }
         }
         __syncthreads();
-        if (D3) {
-            const int per = cells < BLK ? BLK / cells : 1;  // threads per box cell
-            for (int t = threadIdx.x; t < per * cells; t += BLK) {
-                const int l = t % cells, c0 = t / cells;
-                const int lx = l % sx, ly = (l / sx) % sy, lz = l / (sx * sy);
-                const int cz = wrap_int(db.ref[2] + db.lo[2] + lz, nz);
-                const int cy = wrap_int(db.ref[1] + db.lo[1] + ly, ny);
-                const int cx = wrap_int(db.ref[0] + db.lo[0] + lx, nx);
-                double *gcell = Gout + ((int64_t)cz * ny + cy) * nx + cx;
-                for (int comp = c0; comp < NGC; comp += per) {
-                    const int q = comp * cells + l;
-                    double val = 0.0;
-                    for (int r = 0; r < R; r++)
-                        val += acc[r * cstride + q];
-                    if (val != 0.0)
-                        gatomic_add(gcell + (int64_t)comp * nc, val);
-                }
-            }
-        } else {
-            for (int q = threadIdx.x; q < NGC * cells; q += BLK) {
-                const int comp = q / cells, l = q - comp * cells;
-                double val = 0.0;
-                for (int r = 0; r < R; r++)
-                    val += acc[r * cstride + q];
-                if (val != 0.0)
-                    gatomic_add(Gout + (int64_t)comp * nc + wrap_int(db.ref[2] + db.lo[2] + l, nz), val);
-            }
+        for (int q = threadIdx.x; q < NGC * cells; q += BLK) {
+            const int comp = q / cells, l = q - comp * cells;
+            double val = 0.0;
+            for (int r = 0; r < R; r++)
+                val += acc[r * cstride + q];
+            if (val != 0.0)
+                gatomic_add(Gout + (int64_t)comp * nc + box_cell(l), val);
         }
     } else if (active) {
 #pragma unroll
@@ -862,14 +1145,15 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
                     const int cz = wrap_int(df[2] + bz, nz);
                     const int cy = D3 ? wrap_int(df[1] + by, ny) : 0;
                     const int cx = D3 ? wrap_int(df[0] + bx, nx) : 0;
-                    double *g = Gout + ((int64_t)cz * ny + cy) * nx + cx;
+                    const int64_t cell = ((int64_t)cz * ny + cy) * nx + cx, cs = FULL ? nc : 1;
+                    double *g = Gout + (FULL ? cell : cell * NGT);
 #pragma unroll
                     for (int k = 0; k < NCS; k++) {
                         const double xc = w * Xd[k];
-                        gatomic_add(g + (int64_t)k * nc, xc);
-                        gatomic_add(g + (int64_t)(NCS + k) * nc, vx * xc);
-                        gatomic_add(g + (int64_t)(2 * NCS + k) * nc, vy * xc);
-                        gatomic_add(g + (int64_t)(3 * NCS + k) * nc, vz * xc);
+                        gatomic_add(g + (int64_t)k * cs, xc);
+                        gatomic_add(g + (int64_t)(NCS + k) * cs, vx * xc);
+                        gatomic_add(g + (int64_t)(2 * NCS + k) * cs, vy * xc);
+                        gatomic_add(g + (int64_t)(3 * NCS + k) * cs, vz * xc);
                     }
                 }
     }
@@ -938,13 +1222,16 @@ __global__ void __launch_bounds__(256) finalize_kernel(const PDesc *__restrict__
         const int r = (int)((MODE == PM_DEPOSIT ? 4 * n : 4 * n + STG) % 3);
         G = r == 0 ? S.G0 : (r == 1 ? S.G1 : S.G2);
     }
-    const int64_t len = (int64_t)NGC * S.ncell, plane = (int64_t)NG * S.ncell;
+    const int64_t len = (int64_t)NGC * S.ncell;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < len;
          q += (int64_t)gridDim.x * blockDim.x) {
-        const long long hi = S.GL[q], lo = S.GL[plane + q];
-        gst(G + q, from_limbs(hi, lo, S.qi));
-        S.GL[q] = 0;
-        S.GL[plane + q] = 0;
+        const int64_t cell = q / NGC;
+        const int comp = (int)(q - cell * NGC);
+        long long *a = S.GL + cell * 2 * NGC + comp;
+        // (the stage grids per cell, the moments per component)
+        gst(G + (FULL ? comp * S.ncell + cell : q), from_limbs(a[0], a[NGC], S.qi));
+        a[0] = 0;
+        a[NGC] = 0;
     }
 }
 
