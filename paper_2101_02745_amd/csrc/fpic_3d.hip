@@ -118,23 +118,38 @@ __device__ __forceinline__ void axis_shift(double v, double t, double dx, int n,
 // the negated sums of the next two and are not stored).
 __device__ __forceinline__ int kslot(int c) { return c < 9 ? c - 1 : c - 2; }
 
-// The particle streams of the 3D kernels (state, slopes, sources) are all
-// read and written with the streaming (nontemporal) policy: a wave touches
-// whole x-row segments that no other workgroup reads in the same stage, and
-// the arrays (gigabytes) are far larger than the Infinity Cache, so caching
-// them only evicts the grid rows that are re-read (the 64^3 x 92 box: fused
-// stages 10.24 -> 9.60 ms per step, separate kernels 12.55 -> 12.37).  The
-// 1D kernels keep most streams cacheable: there neighbouring tiles share
-// cache lines of the rotated rows, and full streaming was much slower.
+// The particle streams of the fused kernels (state, slopes) are read and
+// written with the streaming (nontemporal) policy: a wave touches a whole
+// x-row, and the arrays (gigabytes) are far larger than the Infinity Cache, so
+// caching them only evicts the grid rows that are re-read (the 64^3 x 92 box:
+// 10.24 -> 9.60 ms per step; rows of 50 and 40 cells, too, are 1 % faster).
+// The separate kernels stream only rows that are whole cache lines (streams()
+// below).  The 1D kernels keep most streams cacheable: there neighbouring
+// tiles share cache lines of the rotated rows, and full streaming was much
+// slower.
 //
-// NT: streaming (nontemporal) loads
-template <bool NT = false>
+// NT: streaming (nontemporal) loads and stores
+template <bool NT>
+__device__ __forceinline__ double pld(const double *p)
+{
+    return NT ? fpic::gld_nt(p) : gld(p);
+}
+template <bool NT>
+__device__ __forceinline__ void pst(double *p, double v)
+{
+    if (NT)
+        fpic::gst_nt(p, v);
+    else
+        gst(p, v);
+}
+
+template <bool NT>
 __device__ __forceinline__ void load_slope(const double *K, int64_t np, int64_t p, bool active, double k[18])
 {
 #pragma unroll
     for (int c = 1; c < 18; c++)
         if (c != 9)
-            k[c] = active ? (NT ? fpic::gld_nt(K + kslot(c) * np + p) : gld(K + kslot(c) * np + p)) : 0.0;
+            k[c] = active ? pld<NT>(K + kslot(c) * np + p) : 0.0;
     k[0] = -(k[1] + k[2]);
     k[9] = -(k[10] + k[11]);
 }
@@ -194,6 +209,7 @@ __device__ __forceinline__ XRow xrow(int nx, int seg, int lane)
 // the moments diagnostic deposits all nine components of its sources.
 constexpr int NXT = 8, NGT = 4 * NXT;
 
+template <bool NT>
 __device__ __forceinline__ void store_source(const Desc3 &S, int64_t p, double wN, double wNb,
                                              const double yn[18])
 {
@@ -201,11 +217,11 @@ __device__ __forceinline__ void store_source(const Desc3 &S, int64_t p, double w
 #pragma unroll
     for (int k = 0; k < 9; k++)
         x[k] = source_comp(k, wN, yn[k], wNb, yn[9 + k]);
-    fpic::gst_nt(S.X + p, x[1] - x[0]);
-    fpic::gst_nt(S.X + S.np + p, x[2] - x[0]);
+    pst<NT>(S.X + p, x[1] - x[0]);
+    pst<NT>(S.X + S.np + p, x[2] - x[0]);
 #pragma unroll
     for (int k = 3; k < 9; k++)
-        fpic::gst_nt(S.X + (k - 1) * S.np + p, x[k]);
+        pst<NT>(S.X + (k - 1) * S.np + p, x[k]);
 }
 
 // MODE 1..4: Runge-Kutta stages; 5: deposit sources of the current state.
@@ -220,7 +236,21 @@ __device__ __forceinline__ void store_source(const Desc3 &S, int64_t p, double w
 // interpolation and takes the particles in storage order.
 constexpr int MAX_WAVES3 = 8;
 
-template <int MODE>
+// The work item of block b of n: consecutive blocks go to the eight XCDs in
+// turn, so every XCD takes a run of consecutive items.  For the segments of
+// long rows, whose ends share cache lines, and for the deposits' patches, which
+// share source rows (150 x 40 x 32 cells x 24 directions: 3.74 -> 3.44 ms per
+// step).  Whole rows of the particle kernels share few lines, and neighbouring
+// rows on all XCDs at once use the memory channels better (50 x 44 x 36 x 24
+// quadratic 2.02 ms, in runs 2.07).
+constexpr int XCDS = 8;
+__device__ __forceinline__ int xcd_item(int b, int n)
+{
+    const int x = b % XCDS, i = b / XCDS, q = n / XCDS, r = n % XCDS;
+    return x * q + min(x, r) + i;
+}
+
+template <int MODE, bool NT>
 __global__ void __launch_bounds__(MAX_WAVES3 * W)
 particle3d_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
 {
@@ -229,7 +259,7 @@ particle3d_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
     const int lane = threadIdx.x & (W - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
     const int nwaves = blockDim.x / W;
-    const int item = blockIdx.x;
+    const int item = S.n[0] > W ? xcd_item(blockIdx.x, nitems) : (int)blockIdx.x;
     if (item >= nitems)
         return;  // whole workgroup: uniform
     const int nx = S.n[0], ny = S.n[1], nz = S.n[2];
@@ -292,7 +322,7 @@ particle3d_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
         double Y[18];
 #pragma unroll
         for (int k = 0; k < 18; k++)
-            Y[k] = active ? fpic::gld_nt(S.Y + k * S.np + p) : 0.0;
+            Y[k] = active ? pld<NT>(S.Y + k * S.np + p) : 0.0;
         double yn[18];
         if (MODE == 5) {
 #pragma unroll
@@ -337,9 +367,9 @@ particle3d_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
             } else if (MODE == 4) {
                 const double h6 = dt / 6.0;
                 double k1[18], k2[18], k3[18];
-                load_slope<true>(S.K1, S.np, p, active, k1);
-                load_slope<true>(S.K2, S.np, p, active, k2);
-                load_slope<true>(S.K3, S.np, p, active, k3);
+                load_slope<NT>(S.K1, S.np, p, active, k1);
+                load_slope<NT>(S.K2, S.np, p, active, k2);
+                load_slope<NT>(S.K3, S.np, p, active, k3);
 #pragma unroll
                 for (int k = 0; k < 18; k++) {
                     yv[k] = Y[k] + dt * k3[k];
@@ -348,7 +378,7 @@ particle3d_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
                 }
             } else {
                 double kp[18];
-                load_slope<true>(Kp, S.np, p, active, kp);
+                load_slope<NT>(Kp, S.np, p, active, kp);
 #pragma unroll
                 for (int k = 0; k < 18; k++) {
                     yv[k] = Y[k] + a * kp[k];
@@ -370,7 +400,7 @@ particle3d_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
                 for (int k = 0; k < 18; k++) {
                     yn[k] = base[k] + h6 * kk[k];
                     if (active)
-                        fpic::gst_nt(S.Y + k * S.np + p, yn[k]);
+                        pst<NT>(S.Y + k * S.np + p, yn[k]);
                 }
             } else {
                 double *Ko = (MODE == 1) ? S.K1 : (MODE == 2) ? S.K2 : S.K3;
@@ -378,13 +408,13 @@ particle3d_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
 #pragma unroll
                 for (int k = 0; k < 18; k++) {
                     if (active && k != 0 && k != 9)
-                        fpic::gst_nt(Ko + kslot(k) * S.np + p, kk[k]);
+                        pst<NT>(Ko + kslot(k) * S.np + p, kk[k]);
                     yn[k] = base[k] + an * kk[k];
                 }
             }
         }
         if (active)
-            store_source(S, p, wN, wNb, yn);
+            store_source<NT>(S, p, wN, wNb, yn);
     }
 }
 
@@ -499,7 +529,8 @@ deposit3d_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
     const int nx = S.n[0], ny = S.n[1], nz = S.n[2];
     const int nseg = xsegs(nx, W - 1);
-    const int patch = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    const int bi = xcd_item(blockIdx.x, gridDim.x);
+    const int patch = bi / nseg, seg = bi % nseg;
     const int npy = (ny + DEP_PY - 1) / DEP_PY;
     const int y = (patch % npy) * DEP_PY + wave % DEP_PY;
     const int z = (patch / npy) * DEP_PZ + wave / DEP_PY;
@@ -538,6 +569,16 @@ deposit3d_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
             gst(G + (int64_t)q * S.ncell + cell, acc[q]);
     }
 }
+
+// Whether the separate kernels read and write the particles with the streaming
+// policy: rows of one wave and whole 128-byte lines (64^3 x 92 linear 12.55 ->
+// 12.37 ms per step).  Otherwise neighbouring waves share the lines at the ends
+// of their rows or segments, which then stay in L2 until both have used them
+// (with segments on the same XCD, see xcd_item): 150 x 40 x 32 cells x 24
+// directions 3.74 -> 3.09 ms per step (streaming, 3.43), 130 x 40 x 40 x 92
+// 16.4 -> 13.5 ms, 100 x 40 x 40 x 24 quadratic 3.85 -> 3.55 ms, 50 x 44 x 36 x
+// 24 quadratic 2.04 -> 2.02 ms.
+static bool streams(const Desc3 &h) { return h.n[0] <= W && h.n[0] % 16 == 0; }
 
 // workgroups of a deposit launch: patches of rows times x-segments (segments
 // of 63 cells for the linear shape, 62 for the quadratic one)
@@ -659,7 +700,7 @@ __device__ __forceinline__ void load_slope_raw(const double *K, int64_t np, int6
 #pragma unroll
     for (int c = 1; c < 18; c++)
         if (c != 9)
-            k[c] = NT ? fpic::gld_nt(K + kslot(c) * np + p) : gld(K + kslot(c) * np + p);
+            k[c] = pld<NT>(K + kslot(c) * np + p);
 }
 
 __device__ __forceinline__ void slope_trace(double k[18])
@@ -1107,6 +1148,14 @@ __device__ __forceinline__ int wrap(int i, int n)
     return i < 0 ? i + n : i;
 }
 
+// i mod n for -2 n <= i < 2 n
+__device__ __forceinline__ int wrap1(int i, int n)
+{
+    i = i < 0 ? i + n : i;
+    i = i < 0 ? i + n : i;
+    return i >= n ? i - n : i;
+}
+
 // w[b] for a run-time b in 0..2, without indexing a private array
 __device__ __forceinline__ double pick3(const double w[3], int b)
 {
@@ -1119,7 +1168,7 @@ __device__ __forceinline__ double pick3(const double w[3], int b)
 template <int MODE>
 constexpr int qdb() { return MODE == 4 ? 1 : 2; }
 
-template <int MODE>
+template <int MODE, bool NT>
 __global__ void __launch_bounds__(MAX_WAVES3 * W)
 particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
 {
@@ -1128,7 +1177,7 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
     const int lane = threadIdx.x & (W - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
     const int nwaves = blockDim.x / W;
-    const int item = blockIdx.x;
+    const int item = S.n[0] > W ? xcd_item(blockIdx.x, nitems) : (int)blockIdx.x;
     if (item >= nitems)
         return;
     const int nx = S.n[0], ny = S.n[1], nz = S.n[2];
@@ -1262,13 +1311,13 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
                 for (int k = 1; k < 9; k++)
                     Hnn[k] = m ? Hb4[jj][k - 1] : Hnn[k];
             }
-            const int cx = wrap(xw.x - rx, nx), cy = wrap(y0 - ry, ny), cz = wrap(z0 - rz, nz);
+            const int cx = wrap1(xw.x - rx, nx), cy = wrap1(y0 - ry, ny), cz = wrap1(z0 - rz, nz);
             const int64_t c = ((int64_t)cz * ny + cy) * nx + (active ? cx : 0);
             const int64_t p = (int64_t)d * S.ncell + c;
             double Y[18];
 #pragma unroll
             for (int k = 0; k < 18; k++)
-                Y[k] = active ? fpic::gld_nt(S.Y + k * S.np + p) : 0.0;
+                Y[k] = active ? pld<NT>(S.Y + k * S.np + p) : 0.0;
             double yv[18], base[18], yn[18];
             if (MODE == 1) {
 #pragma unroll
@@ -1279,12 +1328,12 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
                 // registers than holding all three)
                 const double h6 = dt / 6.0;
                 double ks[18], kt[18];
-                load_slope<true>(S.K1, S.np, p, active, ks);
-                load_slope<true>(S.K2, S.np, p, active, kt);
+                load_slope<NT>(S.K1, S.np, p, active, ks);
+                load_slope<NT>(S.K2, S.np, p, active, kt);
 #pragma unroll
                 for (int k = 0; k < 18; k++)
                     ks[k] = ks[k] + 2.0 * kt[k];
-                load_slope<true>(S.K3, S.np, p, active, kt);
+                load_slope<NT>(S.K3, S.np, p, active, kt);
 #pragma unroll
                 for (int k = 0; k < 18; k++) {
                     yv[k] = Y[k] + dt * kt[k];
@@ -1292,7 +1341,7 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
                 }
             } else {
                 double kp[18];
-                load_slope<true>(Kp, S.np, p, active, kp);
+                load_slope<NT>(Kp, S.np, p, active, kp);
 #pragma unroll
                 for (int k = 0; k < 18; k++) {
                     yv[k] = Y[k] + 0.5 * dt * kp[k];
@@ -1314,7 +1363,7 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
                 for (int k = 0; k < 18; k++) {
                     yn[k] = base[k] + h6 * kk[k];
                     if (active)
-                        fpic::gst_nt(S.Y + k * S.np + p, yn[k]);
+                        pst<NT>(S.Y + k * S.np + p, yn[k]);
                 }
             } else {
                 double *Ko = (MODE == 1) ? S.K1 : (MODE == 2) ? S.K2 : S.K3;
@@ -1322,12 +1371,12 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
 #pragma unroll
                 for (int k = 0; k < 18; k++) {
                     if (active && k != 0 && k != 9)
-                        fpic::gst_nt(Ko + kslot(k) * S.np + p, kk[k]);
+                        pst<NT>(Ko + kslot(k) * S.np + p, kk[k]);
                     yn[k] = base[k] + an * kk[k];
                 }
             }
             if (active)
-                store_source(S, p, wN, wNb, yn);
+                store_source<NT>(S, p, wN, wNb, yn);
         }
     }
 }
@@ -1345,7 +1394,8 @@ deposit3q_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
     const int nx = S.n[0], ny = S.n[1], nz = S.n[2];
     const int nseg = xsegs(nx, W - 2);
-    const int patch = blockIdx.x / nseg, seg = blockIdx.x % nseg;
+    const int bi = xcd_item(blockIdx.x, gridDim.x);
+    const int patch = bi / nseg, seg = bi % nseg;
     const int npy = (ny + DEP_PY - 1) / DEP_PY;
     const int y = (patch % npy) * DEP_PY + wave % DEP_PY;
     const int z = (patch / npy) * DEP_PZ + wave / DEP_PY;
@@ -1371,7 +1421,12 @@ deposit3q_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
         axis_quad(vx, t, S.dx[0], nx, &rx, wx);
         axis_quad(vy, t, S.dx[1], ny, &ry, wy);
         axis_quad(vz, t, S.dx[2], nz, &rz, wz);
-        const int xs = wrap(xw.x - rx, nx);
+        // the same for the whole wave: row addresses in scalar registers
+        rx = __builtin_amdgcn_readfirstlane(rx);
+        ry = __builtin_amdgcn_readfirstlane(ry);
+        rz = __builtin_amdgcn_readfirstlane(rz);
+        const int xs = wrap1(xw.x - rx, nx);
+        const int yb = wrap1(y + 1 - ry, ny), zb = wrap1(z + 1 - rz, nz);
         double Xyz[NC];
 #pragma unroll
         for (int k = 0; k < NC; k++)
@@ -1380,7 +1435,7 @@ deposit3q_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
         for (int kk = 0; kk < 3; kk++)
 #pragma unroll
             for (int j = 0; j < 3; j++) {
-                const int yy = wrap(y - j + 1 - ry, ny), zz = wrap(z - kk + 1 - rz, nz);
+                const int yy = wrap1(yb - j, ny), zz = wrap1(zb - kk, nz);
                 const double w = wy[j] * wz[kk];
                 const double *xp = S.X + (int64_t)d * S.ncell + ((int64_t)zz * ny + yy) * nx + xs;
 #pragma unroll
@@ -1657,7 +1712,8 @@ int workspace_bytes(const fpic_config &cfg, const fpic_tuning *tune, size_t *byt
 
 // stage `mode` (1..4; 5 = deposit sources of the current state) of the
 // particle kernels, and the deposit of the sources, for the box's shape order
-static void launch_particle(const Ctx3D *c, int mode, hipStream_t s)
+template <bool NT>
+static void launch_particle_nt(const Ctx3D *c, int mode, hipStream_t s)
 {
     // MODE 5 is the linear kernel in both shapes: its own x-segments
     const int items5 = c->h.n[1] * c->h.n[2] * xsegs(c->h.n[0], W - 1) * c->ngroup;
@@ -1665,25 +1721,33 @@ static void launch_particle(const Ctx3D *c, int mode, hipStream_t s)
     const bool q = c->h.shape == 2;
     switch (mode) {
     case 1:
-        if (q) particle3q_kernel<1><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
-        else particle3d_kernel<1><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
+        if (q) particle3q_kernel<1, NT><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
+        else particle3d_kernel<1, NT><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
         break;
     case 2:
-        if (q) particle3q_kernel<2><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
-        else particle3d_kernel<2><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
+        if (q) particle3q_kernel<2, NT><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
+        else particle3d_kernel<2, NT><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
         break;
     case 3:
-        if (q) particle3q_kernel<3><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
-        else particle3d_kernel<3><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
+        if (q) particle3q_kernel<3, NT><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
+        else particle3d_kernel<3, NT><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
         break;
     case 4:
-        if (q) particle3q_kernel<4><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
-        else particle3d_kernel<4><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
+        if (q) particle3q_kernel<4, NT><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
+        else particle3d_kernel<4, NT><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, c->nitems);
         break;
     default:  // no interpolation: the same for both shapes
-        particle3d_kernel<5><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, items5);
+        particle3d_kernel<5, NT><<<pgrid, pblk, 0, s>>>(c->d, c->dpw, items5);
         break;
     }
+}
+
+static void launch_particle(const Ctx3D *c, int mode, hipStream_t s)
+{
+    if (streams(c->h))
+        launch_particle_nt<true>(c, mode, s);
+    else
+        launch_particle_nt<false>(c, mode, s);
 }
 
 // The stage deposits (traceless sources, NGT grid components); full = true
