@@ -1488,28 +1488,27 @@ __global__ void tick3d(const Desc3 *dp)
         *dp->step += 1;
 }
 
+// block (b, k): component k
 __global__ void __launch_bounds__(256) totals3d(const Desc3 *dp, double *partial)
 {
     const Desc3 &S = *dp;
     __shared__ double sh[256];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int k = 0; k < 18; ++k) {
-        double s = 0.0;
-        for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < S.np; p += stride) {
-            const int d = (int)(p / S.ncell);
-            s += ((k < 9) ? tld(S.Nw, d) : tld(S.Nbw, d)) * S.Y[k * S.np + p];
-        }
-        sh[threadIdx.x] = s;
-        __syncthreads();
-        for (int h = 128; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h)
-                sh[threadIdx.x] += sh[threadIdx.x + h];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0)
-            partial[(size_t)blockIdx.x * 18 + k] = sh[0];
+    const int k = blockIdx.y;
+    double s = 0.0;
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < S.np; p += stride) {
+        const int d = (int)(p / S.ncell);
+        s += ((k < 9) ? tld(S.Nw, d) : tld(S.Nbw, d)) * S.Y[k * S.np + p];
+    }
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h)
+            sh[threadIdx.x] += sh[threadIdx.x + h];
         __syncthreads();
     }
+    if (threadIdx.x == 0)
+        partial[(size_t)blockIdx.x * 18 + k] = sh[0];
 }
 
 __global__ void __launch_bounds__(256) check3d(const Desc3 *dp, double *partial)
@@ -1551,6 +1550,8 @@ __global__ void finish_sums(const double *partial, int nblk, int width, int is_c
     if (k >= width)
         return;
     double s = 0.0;
+    // (the sums are one chain, their loads sixteen at a time)
+#pragma unroll 16
     for (int b = 0; b < nblk; ++b) {
         const double v = partial[(size_t)b * width + k];
         s = (is_check && k < 2) ? fmax(s, v) : s + v;
@@ -2053,7 +2054,7 @@ int flavor_totals(Ctx3D *c, double *out)
     if (!c->state_set)
         return fail(FPIC_ESTATE, "flavor_totals before set_state");
     double *part = c->scratch + 18;
-    totals3d<<<kBlk, 256, 0, c->stream>>>(c->d, part);
+    totals3d<<<dim3(kBlk, 18), 256, 0, c->stream>>>(c->d, part);
     finish_sums<<<1, 64, 0, c->stream>>>(part, kBlk, 18, 0, c->scratch);
     HIPCHECK(hipGetLastError());
     HIPCHECK(hipMemcpyAsync(c->hbuf, c->scratch, sizeof(double) * 18, hipMemcpyDeviceToHost, c->stream));

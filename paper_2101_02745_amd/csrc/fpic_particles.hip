@@ -1423,12 +1423,10 @@ __global__ void unload_kernel(const PDesc *__restrict__ dp, double *out)
 {
     const PDesc &S = *dp;
     const int64_t np = S.np;
+    const int k = blockIdx.y;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < np;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t j = S.pid[i];
-        for (int k = 0; k < 18; k++)
-            out[k * np + j] = S.Y[k * np + i];
-    }
+         i += (int64_t)gridDim.x * blockDim.x)
+        out[k * np + S.pid[i]] = S.Y[k * np + i];
 }
 
 // Flavor totals, summed exactly in limbs like the deposits (the particle
@@ -1943,7 +1941,7 @@ int fpic_particles_get_state(fpic_pctx *c, double *state)
     if (!c->state_set)
         return fail(FPIC_ESTATE, "get_state before set");
     const unsigned nb = (unsigned)std::min<int64_t>(2048, (c->h[0].np + 255) / 256);
-    unload_kernel<<<nb, 256, 0, c->stream>>>(c->d[c->par], state);
+    unload_kernel<<<dim3(nb, 18), 256, 0, c->stream>>>(c->d[c->par], state);
     HIPCHECK(hipGetLastError());
     return FPIC_OK;
 }
