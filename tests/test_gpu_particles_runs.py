@@ -60,3 +60,21 @@ def test_deposit_routes(ncell, ppc, order, every, exact):
     assert_parity(got, ref, what=f"{ncell} ppc {ppc} order {order}")
     if exact:
         assert np.array_equal(got, gpu(np.random.RandomState(3).permutation(keep.size)))
+
+
+@pytest.mark.parametrize("npart", [1, 255, (1 << 18) - 1, 1 << 18, (1 << 18) + 57])
+def test_state_in_the_callers_order(npart):
+    """get_state undoes the sort, component by component or, from 2^18
+    particles on, by whole lines: bit for bit what was set."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2101_02745_amd.particles import ParticleSim
+    rng = np.random.RandomState(5)
+    pos = rng.random_sample((npart, 3)) * (6.0, 5.0, 4.0)
+    dirs = I.directions(26)[np.arange(npart) % 26]
+    state = rng.standard_normal((18, npart))
+    sim = ParticleSim((6, 5, 4), (1.0, 1.0, 1.0), npart, np.zeros((3, 3), complex), 0.1)
+    sim.set(pos, dirs, np.ones(npart), np.ones(npart), state)
+    assert np.array_equal(sim.get_state().cpu().numpy(), state)
+    sim.close()
