@@ -329,35 +329,38 @@ particle3d_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
             for (int k = 0; k < 18; k++)
                 yn[k] = Y[k];
         } else {
-            // y/z interpolation from the four staged rows, then x with the
-            // lane to the right (periodic in x); one group of 8 traceless
-            // components (A, B_x, B_y, B_z) at a time:
-            // Hnn = A - (vx B_x + vy B_y + vz B_z), its ee entry 0
+            // Hnn = A - (vx B_x + vy B_y + vz B_z), its ee entry 0: y/z
+            // interpolation from the four staged rows, one group of 8
+            // traceless components (A, B_x, B_y, B_z) at a time with its
+            // factor, then x with the lane to the right (periodic in x) once
+            // for the sum of the groups
             double wyz[4];
 #pragma unroll
             for (int cz = 0; cz < 2; cz++)
 #pragma unroll
                 for (int cy = 0; cy < 2; cy++)
                     wyz[2 * cz + cy] = (cy ? fy : 1.0 - fy) * (cz ? fz : 1.0 - fz);
-            double Hnn[9];
+            double r[NXT];
 #pragma unroll
-            for (int k = 0; k < 9; k++)
-                Hnn[k] = 0.0;
+            for (int k = 0; k < NXT; k++)
+                r[k] = 0.0;
 #pragma unroll 1
             for (int grp4 = 0; grp4 < 4; grp4++) {
                 const double coef = (grp4 == 0) ? 1.0 : (grp4 == 1) ? -vx : (grp4 == 2) ? -vy : -vz;
+                const double *g = Gt + NXT * grp4 * W + lane;
 #pragma unroll
-                for (int k = 0; k < NXT; k++) {
-                    const double *g = Gt + (NXT * grp4 + k) * W + lane;
-                    double r = 0.0;
+                for (int q = 0; q < 4; q++) {
+                    const double c = coef * wyz[q];
 #pragma unroll
-                    for (int q = 0; q < 4; q++)
-                        r += wyz[q] * (xr.valid ? g[q * NGT * W] : 0.0);
-                    const double nb = lane_get(r, right);
-                    const double val = (1.0 - fx) * r + fx * nb;
-                    Hnn[k + 1] += coef * val;
+                    for (int k = 0; k < NXT; k++)
+                        r[k] += c * (xr.valid ? g[(q * NGT + k) * W] : 0.0);
                 }
             }
+            double Hnn[9];
+            Hnn[0] = 0.0;
+#pragma unroll
+            for (int k = 0; k < NXT; k++)
+                Hnn[k + 1] = (1.0 - fx) * r[k] + fx * lane_get(r[k], right);
             const double a = (MODE == 4) ? dt : 0.5 * dt;
             double yv[18], base[18];
             if (MODE == 1) {
@@ -920,24 +923,27 @@ stage3f_kernel(const Desc3 *__restrict__ dp)
 #pragma unroll
                     for (int sl = 0; sl < 4; sl++)
                         wsl[sl] = F.wyz[sl ^ xm];
-                    double Hnn[9];
+                    double ra[NXT];
 #pragma unroll
-                    for (int k = 0; k < 9; k++)
-                        Hnn[k] = 0.0;
+                    for (int k = 0; k < NXT; k++)
+                        ra[k] = 0.0;
 #pragma unroll 1
                     for (int grp4 = 0; grp4 < 4; grp4++) {
                         const double coef = (grp4 == 0) ? 1.0 : (grp4 == 1) ? -F.vx : (grp4 == 2) ? -F.vy : -F.vz;
+                        const double *g = Gt + NXT * grp4 * W + xa;
 #pragma unroll
-                        for (int k = 0; k < NXT; k++) {
-                            const double *g = Gt + (NXT * grp4 + k) * W + xa;
-                            double ra = 0.0;
+                        for (int sl = 0; sl < 4; sl++) {
+                            const double c = coef * wsl[sl];
 #pragma unroll
-                            for (int sl = 0; sl < 4; sl++)
-                                ra += wsl[sl] * g[sl * NGT * W];
-                            const double rb = lane_above_wrap(ra, lane, nx);
-                            Hnn[k + 1] += coef * ((1.0 - fx) * ra + fx * rb);
+                            for (int k = 0; k < NXT; k++)
+                                ra[k] += c * g[(sl * NGT + k) * W];
                         }
                     }
+                    double Hnn[9];
+                    Hnn[0] = 0.0;
+#pragma unroll
+                    for (int k = 0; k < NXT; k++)
+                        Hnn[k + 1] = (1.0 - fx) * ra[k] + fx * lane_above_wrap(ra[k], lane, nx);
                     double H[9], Hb[9], kk[18];
 #pragma unroll
                     for (int k = 0; k < 9; k++) {
@@ -1244,8 +1250,10 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
             axis_quad(vb[j][1], t_cur, S.dx[1], ny, &ryb[j], wyb[j]);
             axis_quad(vb[j][2], t_cur, S.dx[2], nz, &rzb[j], wzb[j]);
         }
-        // traceless Hnn: components 1..8 of the packed nine (component 0,
-        // the ee entry, is 0)
+        // traceless Hnn = A - v.B: components 1..8 of the packed nine
+        // (component 0, the ee entry, is 0).  y/z interpolation row by row
+        // from LDS, the four groups with their factors into one sum, each read
+        // used by every direction of the block; then x once for the sum.
         double Hb4[QDB][NXT];
 #pragma unroll
         for (int j = 0; j < QDB; j++)
@@ -1254,14 +1262,14 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
                 Hb4[j][k] = 0.0;
 #pragma unroll 1
         for (int grp4 = 0; grp4 < 4; grp4++) {
-            // y/z interpolation row by row from LDS, each read used by every
-            // direction of the block
-            double r[QDB][NXT];
+            double wyc[QDB][3];
 #pragma unroll
-            for (int j = 0; j < QDB; j++)
+            for (int j = 0; j < QDB; j++) {
+                const double coef = (grp4 == 0) ? 1.0 : -pick3(vb[j], grp4 - 1);
 #pragma unroll
-                for (int k = 0; k < NXT; k++)
-                    r[j][k] = 0.0;
+                for (int b = 0; b < 3; b++)
+                    wyc[j][b] = coef * wyb[j][b];
+            }
 #pragma unroll 3
             for (int q = 0; q < 9; q++) {
                 const int b = q % 3, cc = q / 3;
@@ -1272,22 +1280,20 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
                     gv[k] = gp[k * W];
 #pragma unroll
                 for (int j = 0; j < QDB; j++) {
-                    const double wq = pick3(wyb[j], b) * pick3(wzb[j], cc);
+                    const double wq = pick3(wyc[j], b) * pick3(wzb[j], cc);
 #pragma unroll
                     for (int k = 0; k < NXT; k++)
-                        r[j][k] += wq * gv[k];
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < QDB; j++) {
-                const double coef = (grp4 == 0) ? 1.0 : -pick3(vb[j], grp4 - 1);
-#pragma unroll
-                for (int k = 0; k < NXT; k++) {
-                    const double nl = lane_get(r[j][k], xl), nr = lane_get(r[j][k], xr);
-                    Hb4[j][k] += coef * ((wxb[j][0] * nl + wxb[j][1] * r[j][k]) + wxb[j][2] * nr);
+                        Hb4[j][k] += wq * gv[k];
                 }
             }
         }
+#pragma unroll
+        for (int j = 0; j < QDB; j++)
+#pragma unroll
+            for (int k = 0; k < NXT; k++) {
+                const double r = Hb4[j][k], nl = lane_get(r, xl), nr = lane_get(r, xr);
+                Hb4[j][k] = (wxb[j][0] * nl + wxb[j][1] * r) + wxb[j][2] * nr;
+            }
 
 #pragma unroll 1
         for (int j = 0; j < QDB; j++) {
