@@ -9,13 +9,13 @@
 // deposit source X = (N/dV) rho - (Nbar/dV) rhobar^* (its traceless part: 8
 // reals per particle, see NXT below).
 //
-// deposit kernel (one wave = one x-row of destination cells, all directions
-// in a fixed order; a workgroup holds a small patch of neighbouring rows):
+// deposit kernel (one wave = one x-row of destination cells, all directions, or
+// in boxes of few rows a quarter of them, in a fixed order):
 // every cell pulls X from the eight particles whose next-stage positions
 // straddle it (four rows in y and z, then the lane one to the left in x)
 // with the same weights, and accumulates the combined moments (32 traceless
 // components; 36 for the moments diagnostic) in registers.  Each cell is
-// written once: no atomics, no partial sums, bitwise reproducible.
+// written once, without atomics: bitwise reproducible.
 //
 // Positions are implicit as in 1D: particle (d, c) is at cell c shifted by
 // floor(Omega_a t / dx_a) along each axis with fraction Omega_a t / dx_a minus
@@ -423,7 +423,7 @@ particle3d_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
 
 // Deposit of the sources at the positions of time t = (n + cnext) dt
 // (cnext_num / 2 steps after step n's start; 2 means the next step).
-// Each wave owns one x-row of destination cells and sweeps every direction
+// Each wave owns one x-row of destination cells and sweeps its directions
 // in ascending order; per direction it interpolates the sources of the four
 // rows in y and z, then in x with the lane to the left (accumulate).  The
 // loop is software-pipelined: the 4 NC source values of direction d + 1
@@ -516,29 +516,74 @@ __device__ __forceinline__ void accumulate(const Pull<NC> &o, int left, double a
     }
 }
 
-// A deposit workgroup covers a patch of DEP_PY x DEP_PZ destination rows,
-// one wave per row; its waves sweep the directions in the same order, so
-// the source rows they share (a patch of (DEP_PY + 1) x (DEP_PZ + 1) rows
-// per direction) are mostly read from memory once.
-constexpr int DEP_PY = 2, DEP_PZ = 2;
-constexpr int DEP_WAVES = DEP_PY * DEP_PZ;
+// A deposit workgroup has four waves.  In a box with many rows it covers a
+// patch of 2 x 2 destination rows, one wave per row; its waves sweep the
+// directions in the same order, so the source rows they share (a patch of
+// 3 x 3 rows per direction) are mostly read from memory once.  With fewer rows
+// the waves would be too few to keep enough loads in flight: then the four waves
+// share a row (DS = 4), each sweeping a run of the directions, and their sums
+// are added in the order of the runs.
+constexpr int DEP_WAVES = 4;
+template <int DS>
+constexpr int dep_py() { return DS == 1 ? 2 : 1; }
+template <int DS>
+constexpr int dep_pz() { return DS == 1 ? 2 : 1; }
 
-template <int NC>
+// the wave's row, x-segment and run of directions [d0, d1); none: d0 = d1
+struct DepWave {
+    int row, y, z, seg, slice, d0, d1;
+    bool any;  // the row exists
+};
+template <int DS>
+__device__ __forceinline__ DepWave dep_wave(int ny, int nz, int nseg, int ndir)
+{
+    constexpr int PY = dep_py<DS>(), PZ = dep_pz<DS>(), ROWS = PY * PZ;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
+    const int bi = xcd_item(blockIdx.x, gridDim.x);
+    const int patch = bi / nseg, npy = (ny + PY - 1) / PY;
+    DepWave o;
+    o.seg = bi % nseg;
+    o.row = wave % ROWS;
+    o.slice = wave / ROWS;
+    o.y = (patch % npy) * PY + o.row % PY;
+    o.z = (patch / npy) * PZ + o.row / PY;
+    o.any = o.y < ny && o.z < nz;
+    o.d0 = o.any ? (int)((int64_t)ndir * o.slice / DS) : 0;
+    o.d1 = o.any ? (int)((int64_t)ndir * (o.slice + 1) / DS) : 0;
+    return o;
+}
+
+// adds the sums of a row's waves; false in all but the first of them
+template <int DS, int NA>
+__device__ __forceinline__ bool dep_join(const DepWave &w, int lane, double acc[NA])
+{
+    if (DS == 1)
+        return w.any;
+    constexpr int ROWS = dep_py<DS>() * dep_pz<DS>();
+    __shared__ double sh[DS == 1 ? 1 : (DS - 1) * ROWS * NA * W];
+    if (w.slice > 0)
+#pragma unroll
+        for (int q = 0; q < NA; q++)
+            sh[(((w.slice - 1) * ROWS + w.row) * NA + q) * W + lane] = acc[q];
+    __syncthreads();
+    if (w.slice > 0)
+        return false;
+    for (int t = 0; t < DS - 1; t++)
+#pragma unroll
+        for (int q = 0; q < NA; q++)
+            acc[q] += sh[((t * ROWS + w.row) * NA + q) * W + lane];
+    return w.any;
+}
+
+template <int NC, int DS>
 __global__ void __launch_bounds__(DEP_WAVES * W)
 deposit3d_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
 {
     const Desc3 S = *dp;
     const int lane = threadIdx.x & (W - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
     const int nx = S.n[0], ny = S.n[1], nz = S.n[2];
-    const int nseg = xsegs(nx, W - 1);
-    const int bi = xcd_item(blockIdx.x, gridDim.x);
-    const int patch = bi / nseg, seg = bi % nseg;
-    const int npy = (ny + DEP_PY - 1) / DEP_PY;
-    const int y = (patch % npy) * DEP_PY + wave % DEP_PY;
-    const int z = (patch / npy) * DEP_PZ + wave / DEP_PY;
-    if (y >= ny || z >= nz)
-        return;  // no workgroup barrier in this kernel
+    const DepWave dw = dep_wave<DS>(ny, nz, xsegs(nx, W - 1), S.ndir);
+    const int y = dw.y, z = dw.z, seg = dw.seg;
     const XRow xr = xrow<1, 0>(nx, seg, lane);
     const int64_t n0 = *S.step;
     // half_steps: 0 -> t_n, 1 -> t_n + dt/2, 2 -> t_n + dt (stage 4 of step
@@ -554,16 +599,18 @@ deposit3d_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
     for (int q = 0; q < 4 * NC; q++)
         acc[q] = 0.0;
     DepDir<NC> nxt;
-    if (S.ndir > 0)
-        dep_load<NC>(S, 0, t, y, z, xr.x, nxt);
-    for (int d = 0; d < S.ndir; ++d) {
+    if (dw.d0 < dw.d1)
+        dep_load<NC>(S, dw.d0, t, y, z, xr.x, nxt);
+    for (int d = dw.d0; d < dw.d1; ++d) {
         const DepDir<NC> cur = nxt;
-        if (d + 1 < S.ndir)
+        if (d + 1 < dw.d1)
             dep_load<NC>(S, d + 1, t, y, z, xr.x, nxt);
         Pull<NC> a;
         pull_dir<NC>(cur, xr.valid, a);
         accumulate<NC>(a, left, acc);
     }
+    if (!dep_join<DS, 4 * NC>(dw, lane, acc))
+        return;
     if (xr.own) {
         double *G = out_buf ? S.G[1] : S.G[0];  // (no dynamic index into the descriptor)
         const int64_t cell = ((int64_t)z * ny + y) * nx + xr.x;
@@ -583,12 +630,30 @@ deposit3d_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
 // 24 quadratic 2.04 -> 2.02 ms.
 static bool streams(const Desc3 &h) { return h.n[0] <= W && h.n[0] % 16 == 0; }
 
+// Waves that share a destination row in the deposits: four up to 1.25 times the
+// rows that the chip holds with one wave each (its registers allow 8 waves of
+// the linear kernel and 12 of the quadratic one on each of 256 CUs), above that
+// one.  Per step, one wave a row against four: 12 x 10 x 14 cells x 50
+// directions quadratic (140 rows) 1010 -> 456 us, 70 x 8 x 8 x 12 (128) 161 ->
+// 106, 50 x 44 x 36 x 24 quadratic (1584) 1885 -> 1839, 100 x 36 x 30 x 24 (2160)
+// 1872 -> 1814, 100 x 40 x 40 x 24 quadratic (3200) 3369 -> 3275; but 100 x 50 x
+// 30 x 24 (3000) 2435 and 2455, 150 x 40 x 32 x 24 (3840) 3037 and 3060, 64^3 x 92
+// quadratic (4096) 14.86 and 15.37 ms.
+static int deposit_slices(const Desc3 &h)
+{
+    const bool quad = h.shape == 2;
+    const int64_t rows = (int64_t)h.n[1] * h.n[2] * xsegs(h.n[0], quad ? W - 2 : W - 1);
+    const int64_t held = 256 * (quad ? 12 : 8);
+    return 4 * rows <= 5 * held ? 4 : 1;
+}
+
 // workgroups of a deposit launch: patches of rows times x-segments (segments
 // of 63 cells for the linear shape, 62 for the quadratic one)
+template <int DS>
 static unsigned deposit_blocks(const Desc3 &h)
 {
     const int sw = (h.shape == 2) ? W - 2 : W - 1;
-    return (unsigned)(((h.n[1] + DEP_PY - 1) / DEP_PY) * ((h.n[2] + DEP_PZ - 1) / DEP_PZ) *
+    return (unsigned)(((h.n[1] + dep_py<DS>() - 1) / dep_py<DS>()) * ((h.n[2] + dep_pz<DS>() - 1) / dep_pz<DS>()) *
                       xsegs(h.n[0], sw));
 }
 
@@ -1391,22 +1456,15 @@ particle3q_kernel(const Desc3 *__restrict__ dp, int dpw, int nitems)
 // wx[i] wy[j] wz[k] from the particle whose nearest cell is
 // (x - i + 1, y - j + 1, z - k + 1), i, j, k = 0..2: nine source rows in y
 // and z, then the lanes one right and one left in x.
-template <int NC>
+template <int NC, int DS>
 __global__ void __launch_bounds__(DEP_WAVES * W)
 deposit3q_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
 {
     const Desc3 S = *dp;
     const int lane = threadIdx.x & (W - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
     const int nx = S.n[0], ny = S.n[1], nz = S.n[2];
-    const int nseg = xsegs(nx, W - 2);
-    const int bi = xcd_item(blockIdx.x, gridDim.x);
-    const int patch = bi / nseg, seg = bi % nseg;
-    const int npy = (ny + DEP_PY - 1) / DEP_PY;
-    const int y = (patch % npy) * DEP_PY + wave % DEP_PY;
-    const int z = (patch / npy) * DEP_PZ + wave / DEP_PY;
-    if (y >= ny || z >= nz)
-        return;  // no workgroup barrier in this kernel
+    const DepWave dw = dep_wave<DS>(ny, nz, xsegs(nx, W - 2), S.ndir);
+    const int y = dw.y, z = dw.z, seg = dw.seg;
     const XRow xw = xrow<1, 1>(nx, seg, lane);
     const bool active = xw.valid;
     const int64_t n0 = *S.step;
@@ -1420,7 +1478,7 @@ deposit3q_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
 #pragma unroll
     for (int q = 0; q < 4 * NC; q++)
         acc[q] = 0.0;
-    for (int d = 0; d < S.ndir; ++d) {
+    for (int d = dw.d0; d < dw.d1; ++d) {
         const double vx = tld(S.v[0], d), vy = tld(S.v[1], d), vz = tld(S.v[2], d);
         int rx, ry, rz;
         double wx[3], wy[3], wz[3];
@@ -1458,6 +1516,8 @@ deposit3q_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
             acc[3 * NC + k] += vz * xc;
         }
     }
+    if (!dep_join<DS, 4 * NC>(dw, lane, acc))
+        return;
     if (xw.own) {
         double *G = out_buf ? S.G[1] : S.G[0];
         const int64_t cell = ((int64_t)z * ny + y) * nx + xw.x;
@@ -1757,23 +1817,32 @@ static void launch_particle(const Ctx3D *c, int mode, hipStream_t s)
         launch_particle_nt<false>(c, mode, s);
 }
 
+template <int DS>
+static void launch_deposit_ds(const Ctx3D *c, const Desc3 *dd, int half_steps, int out_buf, hipStream_t s, bool full)
+{
+    const dim3 dgrid(deposit_blocks<DS>(c->h)), blk(DEP_WAVES * W);
+    if (c->h.shape == 2) {
+        if (full)
+            deposit3q_kernel<9, DS><<<dgrid, blk, 0, s>>>(dd, half_steps, out_buf);
+        else
+            deposit3q_kernel<NXT, DS><<<dgrid, blk, 0, s>>>(dd, half_steps, out_buf);
+    } else {
+        if (full)
+            deposit3d_kernel<9, DS><<<dgrid, blk, 0, s>>>(dd, half_steps, out_buf);
+        else
+            deposit3d_kernel<NXT, DS><<<dgrid, blk, 0, s>>>(dd, half_steps, out_buf);
+    }
+}
+
 // The stage deposits (traceless sources, NGT grid components); full = true
 // for the moments diagnostic (all nine source components, 36 per cell).
 static void launch_deposit(const Ctx3D *c, const Desc3 *dd, int half_steps, int out_buf, hipStream_t s,
                            bool full = false)
 {
-    const dim3 dgrid(deposit_blocks(c->h)), blk(DEP_WAVES * W);
-    if (c->h.shape == 2) {
-        if (full)
-            deposit3q_kernel<9><<<dgrid, blk, 0, s>>>(dd, half_steps, out_buf);
-        else
-            deposit3q_kernel<NXT><<<dgrid, blk, 0, s>>>(dd, half_steps, out_buf);
-    } else {
-        if (full)
-            deposit3d_kernel<9><<<dgrid, blk, 0, s>>>(dd, half_steps, out_buf);
-        else
-            deposit3d_kernel<NXT><<<dgrid, blk, 0, s>>>(dd, half_steps, out_buf);
-    }
+    if (deposit_slices(c->h) == 4)
+        launch_deposit_ds<4>(c, dd, half_steps, out_buf, s, full);
+    else
+        launch_deposit_ds<1>(c, dd, half_steps, out_buf, s, full);
 }
 
 // fused linear stage `mode` (1..4; 5 = deposit of the current state) and
