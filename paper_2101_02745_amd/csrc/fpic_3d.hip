@@ -238,11 +238,13 @@ constexpr int MAX_WAVES3 = 8;
 
 // The work item of block b of n: consecutive blocks go to the eight XCDs in
 // turn, so every XCD takes a run of consecutive items.  For the segments of
-// long rows, whose ends share cache lines, and for the deposits' patches, which
-// share source rows (150 x 40 x 32 cells x 24 directions: 3.74 -> 3.44 ms per
-// step).  Whole rows of the particle kernels share few lines, and neighbouring
-// rows on all XCDs at once use the memory channels better (50 x 44 x 36 x 24
-// quadratic 2.02 ms, in runs 2.07).
+// long rows, whose ends share cache lines (150 x 40 x 32 cells x 24 directions:
+// 3.74 -> 3.44 ms per step), and for deposits of one row a workgroup, which
+// share source rows (60 x 50 x 50 x 40 quadratic 4.74 -> 4.41 ms).  Whole rows
+// of the particle kernels share few lines, patches of 2 x 2 whole rows in the
+// deposits less than single ones, and neighbours on all XCDs at once use the
+// memory channels better (50 x 44 x 36 x 24 quadratic 2.02 ms, particle kernels
+// in runs 2.07; 64^3 x 92 quadratic 14.75 ms, deposits in runs 14.93).
 constexpr int XCDS = 8;
 __device__ __forceinline__ int xcd_item(int b, int n)
 {
@@ -539,7 +541,7 @@ __device__ __forceinline__ DepWave dep_wave(int ny, int nz, int nseg, int ndir)
 {
     constexpr int PY = dep_py<DS>(), PZ = dep_pz<DS>(), ROWS = PY * PZ;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / W);
-    const int bi = xcd_item(blockIdx.x, gridDim.x);
+    const int bi = nseg > 1 || DS > 1 ? xcd_item(blockIdx.x, gridDim.x) : (int)blockIdx.x;
     const int patch = bi / nseg, npy = (ny + PY - 1) / PY;
     DepWave o;
     o.seg = bi % nseg;
