@@ -77,7 +77,7 @@ PSORT3_BYTES = 48 + PSTATIC3_B + 4
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("fpic_1d.hip", "fpic_device.h", "fpic_internal.h"):
+    for f in ("fpic_1d.hip", "fpic_1d_body.h", "fpic_1d_steps.h", "fpic_device.h", "fpic_internal.h"):
         h.update(open(os.path.join(ROOT, "paper_2101_02745_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
