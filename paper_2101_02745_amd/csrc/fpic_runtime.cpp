@@ -664,7 +664,11 @@ int batch_build(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, void
     b->steps = P.steps && hipGetDevice(&b->device) == hipSuccess && b->device < kMaxStepDevices &&
                steps1d_fits(P.nwork, P.waves, P.shape);
     if (b->steps) {
-        e = hipMemset(b->ws + P.o_bar, 0, sizeof(unsigned) * kBarWords);
+        // (a copy like the tables above, finished when it returns: a memset on
+        // the null stream may still run then, and a non-blocking stream does
+        // not wait for it)
+        const std::vector<unsigned> zero(kBarWords, 0u);
+        e = hipMemcpy(b->ws + P.o_bar, zero.data(), sizeof(unsigned) * kBarWords, hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = hipEventCreateWithFlags(&b->done, hipEventDisableTiming);
         if (e != hipSuccess)
