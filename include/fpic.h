@@ -26,6 +26,10 @@
  *     before the call returns; the caller keeps ownership of everything.
  *   - Device work is enqueued on the stream given at creation (an
  *     hipStream_t passed as void*).  Only functions marked SYNC wait for it.
+ *   - 1D boxes: should workgroups that step a small box together lose one
+ *     another (a wait of 20 s is given up), the state becomes NaN and the
+ *     next SYNC call returns FPIC_EHIP, as do all calls after it: results
+ *     hold once a SYNC call made after them has returned FPIC_OK.
  *   - The caller owns one device workspace per context (size from
  *     fpic_workspace_bytes); the library never allocates device memory.
  *     The workspace must stay allocated until fpic_destroy.

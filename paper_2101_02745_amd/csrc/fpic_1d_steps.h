@@ -35,11 +35,14 @@ namespace {
 
 typedef const __attribute__((address_space(4))) SimDesc cSimDesc;
 
-// Seconds a workgroup waits at a barrier before it gives up (every
-// workgroup is resident, so a wait is microseconds), in ticks of 10 ns.
-constexpr unsigned long long kBarTicks = 20ull * 100000000ull;
-
 typedef __attribute__((address_space(1))) unsigned guint;
+
+// A wait at a barrier is given up: no result of the context is valid any more.
+__device__ __forceinline__ void give_up(const GridBar &b)
+{
+    __hip_atomic_store((guint *)(b.cnt + kBarBad), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(b.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Barrier number gen (from 1) over the grid; false if the wait was given up.
 __device__ __forceinline__ bool grid_sync(const GridBar &b, unsigned gen, int *sflag)
@@ -57,8 +60,8 @@ __device__ __forceinline__ bool grid_sync(const GridBar &b, unsigned gen, int *s
         int ok = 1;
         const unsigned long long t0 = wall_clock64();
         while ((int)(__hip_atomic_load(top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - gen * ngrp) < 0) {
-            if (wall_clock64() - t0 > kBarTicks) {
-                __hip_atomic_store(b.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (wall_clock64() - t0 > b.bar_ticks) {
+                give_up(b);
                 ok = 0;
                 break;
             }
@@ -284,7 +287,7 @@ __device__ __forceinline__ int64_t particle_at(const Item &I, const Shift &s)
 // body for each was 36 KB of code a stage, more than the instruction cache
 // holds for a step.
 template <int SH, bool SERIAL>
-__device__ __forceinline__ void all_steps(const WorkItem *__restrict__ work, const SimDesc *__restrict__ sims,
+__device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, const SimDesc *__restrict__ sims,
                                           int stride, int keep, int nsteps, const GridBar &bar, const Lds &L,
                                           Columns &C, int *sflag, int lo, int hi, int wave, int lane, int nwaves)
 {
@@ -319,7 +322,7 @@ __device__ __forceinline__ void all_steps(const WorkItem *__restrict__ work, con
             if (last && !I.first) {
                 if (SERIAL)
                     continue;
-                return;
+                return true;
             }
             const cSimDesc &S = I.ds[(int64_t)st * stride];
             const int64_t n = n0 + (it >> 2), np = S.np;
@@ -525,14 +528,32 @@ __device__ __forceinline__ void all_steps(const WorkItem *__restrict__ work, con
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             __syncthreads();
         } else if (!last && !grid_sync(bar, bar.gen + (unsigned)it + 1u, sflag)) {
-            return;
+            return false;
         }
+    }
+    return true;
+}
+
+// After a wait that was given up: NaN in every state that the launch was to
+// return (by each workgroup that gives up, the last of them last), so that
+// what is read from the context before the host has looked at the failure
+// word cannot pass for a result.
+__device__ __forceinline__ void spoil(const WorkItem *__restrict__ work, const SimDesc *__restrict__ sims, int end)
+{
+    for (int q = 0; q < (int)gridDim.x; ++q) {
+        if (work[q].tile != 0 || work[q].group != 0)
+            continue;
+        const cSimDesc *S = (const cSimDesc *)(sims + work[q].sim) + end;
+        double *Y = S->Yout;
+        for (int64_t i = threadIdx.x; i < 18 * S->np; i += blockDim.x)
+            xst<true>(Y + i, __longlong_as_double(0x7ff8000000000000ll));
     }
 }
 
 // Whether the launch's workgroups run together: 1, every workgroup is
-// resident; 0, they are not and another workgroup does the work; 2, they are
-// not and this one does it all.
+// resident; 0, they are not and another workgroup does the work (or an earlier
+// launch has given up a wait, and there is nothing to do); 2, they are not and
+// this one does it all.
 //
 // Every workgroup counts itself in; the last one decides for 1.  One that has
 // waited kArriveTicks for that decides against it (the first decision holds):
@@ -556,6 +577,7 @@ __device__ __forceinline__ int run_together(const GridBar &b, int *sflag)
             return false;
         };
         bool mine = false;
+        const unsigned bad = __hip_atomic_load((guint *)(b.cnt + kBarBad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (__hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == target)
             decide(go);
         const unsigned long long t0 = wall_clock64();
@@ -568,7 +590,7 @@ __device__ __forceinline__ int run_together(const GridBar &b, int *sflag)
                 mine = decide(alone);
             __builtin_amdgcn_s_sleep(1);
         }
-        *sflag = cur == go ? 1 : (mine ? 2 : 0);
+        *sflag = bad ? 0 : (cur == go ? 1 : (mine ? 2 : 0));
     }
     __syncthreads();
     const int r = *sflag;
@@ -596,8 +618,9 @@ steps1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ si
     L.pass = L.v + nwaves * 4 + wave * kPart;  // this wave's
     const int how = run_together(bar, &sflag);
     if (how == 1) {
-        all_steps<SH, false>(work, sims, stride, keep, nsteps, bar, L, C, &sflag, (int)blockIdx.x,
-                             (int)blockIdx.x + 1, wave, lane, nwaves);
+        if (!all_steps<SH, false>(work, sims, stride, keep, nsteps, bar, L, C, &sflag, (int)blockIdx.x,
+                                  (int)blockIdx.x + 1, wave, lane, nwaves))
+            spoil(work, sims, (nsteps - 1) * stride);
     } else if (how == 2) {
         all_steps<SH, true>(work, sims, stride, keep, nsteps, bar, L, C, &sflag, 0, (int)gridDim.x, wave, lane,
                             nwaves);

@@ -117,16 +117,18 @@ hipError_t launch_reduce1d(const RedItem *items, int nitems, const SimDesc *sims
 // whether a launch's workgroups run together.  launch, gen: launches and
 // barriers so far (every launch has a known number, so that the counters are
 // never cleared).  arrive_ticks: how long (in 10 ns) a workgroup waits for
-// the others to be resident.  failed: set (host memory) if a resident
-// workgroup then waits longer at a barrier than any step can take, after
-// which no result of the context is valid.
+// the others to be resident.  bar_ticks: how long a resident workgroup then
+// waits at a barrier before it gives up (every workgroup is resident, so a
+// wait is microseconds).  failed: set (host memory, and the word kBarBad of
+// cnt) if one gave up, after which no result of the context is valid: the
+// launch leaves NaN as its state, and later launches do nothing.
 constexpr int kBarStride = 64, kBarGroup = 16, kMaxStepWgs = 256, kMinStepCells = 16;
 constexpr int kBarArrive = kBarStride * (1 + kMaxStepWgs / kBarGroup), kBarMode = kBarArrive + kBarStride;
-constexpr int kBarWords = kBarMode + kBarStride;
+constexpr int kBarBad = kBarMode + kBarStride, kBarWords = kBarBad + kBarStride;
 struct GridBar {
     unsigned *cnt;
     unsigned launch, gen;
-    unsigned long long arrive_ticks;
+    unsigned long long arrive_ticks, bar_ticks;
     int *failed;
 };
 // nsteps steps of every box (4 nsteps barriers) in one launch of one
@@ -160,3 +162,10 @@ int set_arrive_ticks(void *ctx, unsigned long long ticks);
 int fail(int code, const std::string &msg);
 
 }  // namespace fpic
+
+// For tests: the waits, in ticks of 10 ns, of the step launches of a context
+// or (ctx null) a batch: for one another to be resident, and at a barrier.
+struct fpic_ctx;
+struct fpic_batch;
+extern "C" int fpic_test_step_waits(fpic_ctx *ctx, fpic_batch *batch, unsigned long long arrive_ticks,
+                                    unsigned long long bar_ticks);

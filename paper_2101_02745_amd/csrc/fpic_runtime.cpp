@@ -333,6 +333,7 @@ struct fpic_batch {
     // how long its workgroups wait to be resident together before one of them
     // does all the work (in ticks of 10 ns; 1 s)
     unsigned long long arrive_ticks = 100000000ull;
+    unsigned long long bar_ticks = 2000000000ull;  // and at a barrier before it gives up (20 s)
     int device = 0;
     double cell_volume = 1.0;      // of simulation 0
     // reverse mode (single 1D box)
@@ -409,7 +410,7 @@ fpic_batch *g_steps_last[kMaxStepDevices];
 int run_steps(fpic_batch *b, const SimDesc *ds, int stride, int keep, int nsteps)
 {
     const Plan &P = b->plan;
-    const GridBar bar{reinterpret_cast<unsigned *>(b->ws + P.o_bar), b->launches, b->gen, b->arrive_ticks,
+    const GridBar bar{reinterpret_cast<unsigned *>(b->ws + P.o_bar), b->launches, b->gen, b->arrive_ticks, b->bar_ticks,
                       reinterpret_cast<int *>(b->hbuf + kFailed)};
     std::lock_guard<std::mutex> lock(g_steps_mu);
     fpic_batch *&last = g_steps_last[b->device];
@@ -433,6 +434,17 @@ int fpic::set_arrive_ticks(void *ctx, unsigned long long ticks)
     if (!c || !c->b || !c->b->steps)
         return fail(FPIC_EINVAL, "not a context that runs whole steps in one launch");
     c->b->arrive_ticks = ticks;
+    return FPIC_OK;
+}
+
+extern "C" int fpic_test_step_waits(fpic_ctx *ctx, fpic_batch *batch, unsigned long long arrive_ticks,
+                                    unsigned long long bar_ticks)
+{
+    fpic_batch *b = ctx ? ctx->b : batch;
+    if (!b || !b->steps)
+        return fail(FPIC_EINVAL, "not a context that runs whole steps in one launch");
+    b->arrive_ticks = arrive_ticks;
+    b->bar_ticks = bar_ticks;
     return FPIC_OK;
 }
 
@@ -696,6 +708,8 @@ int batch_set_state(fpic_batch *b, int sim, const double *state, int64_t step0)
 {
     if (!b || sim < 0 || sim >= b->plan.nsim || !state)
         return fail(FPIC_EINVAL, "set_state: bad batch, simulation index or state pointer");
+    if (int rc = steps_ok(b))
+        return rc;
     const SimPlan &s = b->plan.sims[sim];
     const SimDesc &D = b->hdesc[sim];
     HIPCHECK(hipMemcpyAsync(D.Y, state, sizeof(double) * 18 * s.np, hipMemcpyDeviceToDevice, b->stream));
@@ -793,6 +807,8 @@ int fpic_batch_get_state(fpic_batch *b, int32_t sim, double *state)
 {
     if (!b || sim < 0 || sim >= b->plan.nsim || !state)
         return fail(FPIC_EINVAL, "get_state: bad batch, simulation index or state pointer");
+    if (int rc = steps_ok(b))
+        return rc;
     const SimDesc &D = b->hdesc[sim];
     HIPCHECK(hipMemcpyAsync(state, D.Y, sizeof(double) * 18 * D.np, hipMemcpyDeviceToDevice, b->stream));
     return FPIC_OK;
@@ -916,6 +932,8 @@ int fpic_moments(fpic_ctx *c, double *out)
     fpic_batch *b = c->b;
     if (!b->state_set[0])
         return fail(FPIC_ESTATE, "moments before set_state");
+    if (int rc = steps_ok(b))
+        return rc;
     int off, n, roff, rn;
     sim_work(b, 0, &off, &n, &roff, &rn);
     const int nc = b->plan.sims[0].ncell;
@@ -992,6 +1010,9 @@ int fpic_domain_averages(fpic_ctx *c, const double *moments, double *out)
     HIPCHECK(launch_domain_sums(moments, nc, nblk, scratch + 24, scratch, s));
     HIPCHECK(hipMemcpyAsync(hbuf, scratch, sizeof(double) * 24, hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
+    if (c->b)
+        if (int rc = steps_ok(c->b))
+            return rc;
     for (int q = 0; q < 24; ++q)
         out[q] = hbuf[q] / (double)nc;
     return FPIC_OK;
@@ -1047,6 +1068,8 @@ int fpic_batch_profile(fpic_batch *b, int32_t nsteps, double *ms)
     for (bool ok : b->state_set)
         if (!ok)
             return fail(FPIC_ESTATE, "profile before set_state");
+    if (int rc = steps_ok(b))
+        return rc;
     const Plan &P = b->plan;
     hipEvent_t ev[9];
     for (auto &e : ev)
@@ -1079,7 +1102,7 @@ int fpic_batch_profile(fpic_batch *b, int32_t nsteps, double *ms)
         (void)hipEventDestroy(e);
     for (int k = 0; k < 8; ++k)
         ms[k] = acc[k] / nsteps;
-    return rc;
+    return rc ? rc : steps_ok(b);
 }
 
 
