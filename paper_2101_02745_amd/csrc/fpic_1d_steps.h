@@ -558,9 +558,9 @@ __device__ __forceinline__ void spoil(const WorkItem *__restrict__ work, const S
 // Every workgroup counts itself in; the last one decides for 1.  One that has
 // waited kArriveTicks for that decides against it (the first decision holds):
 // the others, waiting or yet to start, then end at once, so that no wait
-// depends on a workgroup that cannot start.  Launches of this process follow
-// one another (run_steps on the host), so that this is for other processes'
-// kernels that hold CUs for as long.
+// depends on a workgroup that cannot start.  Launches of this process that run
+// at the same time fit the chip together (steps_reserve on the host), so that
+// this is for other kernels that hold CUs for as long.
 __device__ __forceinline__ int run_together(const GridBar &b, int *sflag)
 {
     if (threadIdx.x == 0) {

@@ -134,9 +134,9 @@ struct GridBar {
 // nsteps steps of every box (4 nsteps barriers) in one launch of one
 // workgroup per work item, one direction per wave; step j uses the
 // descriptors sims + j stride.  keep: the grids and slopes of every stage go
-// to G and K1..K3 (for the adjoint), else only the next stage-1 grid.  No two
-// such launches may run at the same time on a device.  steps1d_fits: whether
-// all workgroups fit the current device at once.
+// to G and K1..K3 (for the adjoint), else only the next stage-1 grid.  Such
+// launches may run at the same time only if all their workgroups fit the
+// device at once.  steps1d_fits: whether one launch's fit the current device.
 bool steps1d_fits(int nwork, int waves, int shape);
 hipError_t launch_steps1d(const WorkItem *work, int nwork, const SimDesc *sims, int stride, int keep,
                           int waves, int shape, int nsteps, const GridBar &bar, hipStream_t s);

@@ -330,6 +330,9 @@ struct fpic_batch {
     bool steps = false;            // whole steps in one launch (fpic_1d_steps.h)
     unsigned launches = 0, gen = 0;  // such launches, and their grid barriers, so far
     hipEvent_t done = nullptr;     // after the latest such launch
+    fpic_batch *steps_next = nullptr;  // (g_steps_head)
+    bool launching = false;        // done not yet recorded for it
+    int cus = 0, steps_held = 0;
     // how long its workgroups wait to be resident together before one of them
     // does all the work (in ticks of 10 ns; 1 s)
     unsigned long long arrive_ticks = 100000000ull;
@@ -382,7 +385,8 @@ int capture_steps(fpic_batch *b, int nsteps, hipGraphExec_t *exec)
 }
 
 // The step graphs; a context that runs whole steps in one launch captures
-// them only if it is stepped while its stream is being captured.
+// them only if it is stepped while its stream is being captured or while
+// other contexts' launches leave no room.
 int ensure_graphs(fpic_batch *b)
 {
     int rc = b->g1 ? FPIC_OK : capture_steps(b, 1, &b->g1);
@@ -399,28 +403,91 @@ int steps_ok(const fpic_batch *b)
     return failed ? fail(FPIC_EHIP, "the workgroups of a step launch did not run together") : FPIC_OK;
 }
 
-// The latest launch of whole steps on each device.  The workgroups of such a
-// launch wait for one another, so two of them must not hold parts of the chip
-// at the same time: a launch waits for the latest one of another context.
-constexpr int kMaxStepDevices = 64;
+// Contexts whose latest launch of whole steps may still run, per device.  The
+// workgroups of such a launch wait for one another, so launches that may run
+// at the same time must fit the chip together.  They do if each workgroup
+// could have a CU of its own on every XCD (the dispatcher hands workgroups to
+// the XCDs in turn, so that n of them take at most ceil(n / kXcds) CUs on
+// each): whatever order they are dispatched in, a place is then left for the
+// next one.  A call that finds no room steps with one launch per stage, which
+// waits for nothing: no stream ever waits for another one's.
+constexpr int kXcds = 8, kMaxStepDevices = 64;
 std::mutex g_steps_mu;
-fpic_batch *g_steps_last[kMaxStepDevices];
+fpic_batch *g_steps_head[kMaxStepDevices];
 
-// nsteps steps of the descriptors ds + j stride in one launch.
+void steps_unlist(fpic_batch *b)
+{
+    for (fpic_batch **p = &g_steps_head[b->device]; *p; p = &(*p)->steps_next)
+        if (*p == b) {
+            *p = b->steps_next;
+            return;
+        }
+}
+
+// Whether a launch of b may start beside those that may still run; if so, b
+// counts among them.  Launches of one stream never run at the same time, so
+// the latest stands for them, with the most that any of them takes
+// (hipStreamPerThread names a stream per thread).
+bool steps_reserve(fpic_batch *b)
+{
+    const int mine = (b->plan.nwork + kXcds - 1) / kXcds * kXcds;
+    std::lock_guard<std::mutex> lock(g_steps_mu);
+    auto same = [&](const fpic_batch *x) {
+        return x == b || (x->stream == b->stream && b->stream != hipStreamPerThread && !x->launching);
+    };
+    auto room = [&]() {
+        int sum = 0;
+        for (fpic_batch *x = g_steps_head[b->device]; x; x = x->steps_next)
+            sum += same(x) ? 0 : x->steps_held;
+        return sum == 0 || sum + mine <= b->cus;
+    };
+    auto drop = [&](auto done) {
+        for (fpic_batch *x = g_steps_head[b->device], *next; x; x = next) {
+            next = x->steps_next;
+            if (done(x))
+                steps_unlist(x);
+        }
+    };
+    if (!room()) {
+        // without the launches that have finished (relaxed mode: another
+        // thread may be capturing)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        drop([](const fpic_batch *x) { return !x->launching && hipEventQuery(x->done) == hipSuccess; });
+        (void)hipGetLastError();  // not ready is no error
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!room())
+            return false;
+    }
+    int held = mine;
+    drop([&](const fpic_batch *x) {
+        if (same(x))
+            held = std::max(held, x->steps_held);
+        return same(x);
+    });
+    b->steps_held = held;
+    b->steps_next = g_steps_head[b->device];
+    g_steps_head[b->device] = b;
+    b->launching = true;
+    return true;
+}
+
+// nsteps steps of the descriptors ds + j stride in one launch, after
+// steps_reserve.
 int run_steps(fpic_batch *b, const SimDesc *ds, int stride, int keep, int nsteps)
 {
     const Plan &P = b->plan;
     const GridBar bar{reinterpret_cast<unsigned *>(b->ws + P.o_bar), b->launches, b->gen, b->arrive_ticks, b->bar_ticks,
                       reinterpret_cast<int *>(b->hbuf + kFailed)};
+    hipError_t e = launch_steps1d(b->dwork, P.nwork, ds, stride, keep, P.waves, P.shape, nsteps, bar, b->stream);
+    if (e == hipSuccess) {
+        b->launches += 1u;
+        b->gen += 4u * (unsigned)nsteps;
+        e = hipEventRecord(b->done, b->stream);
+    }
     std::lock_guard<std::mutex> lock(g_steps_mu);
-    fpic_batch *&last = g_steps_last[b->device];
-    if (last && last != b)
-        HIPCHECK(hipStreamWaitEvent(b->stream, last->done, 0));
-    HIPCHECK(launch_steps1d(b->dwork, P.nwork, ds, stride, keep, P.waves, P.shape, nsteps, bar, b->stream));
-    b->launches += 1u;
-    b->gen += 4u * (unsigned)nsteps;
-    last = b;
-    HIPCHECK(hipEventRecord(b->done, b->stream));
+    b->launching = false;
+    HIPCHECK(e);
     return FPIC_OK;
 }
 
@@ -453,7 +520,6 @@ namespace {
 // The dispatcher hands workgroup b to XCD b % 8, and each XCD has its own
 // L2.  Place item i of the preferred sequence at launch slot b such that
 // every XCD receives one contiguous run of the sequence.
-constexpr int kXcds = 8;
 void xcd_order(const std::vector<WorkItem> &seq, std::vector<WorkItem> &out)
 {
     const size_t n = seq.size();
@@ -674,6 +740,7 @@ int batch_build(int nsim, const fpic_config *cfgs, const fpic_tuning *tune, void
 
     b->hbuf[kFailed] = 0.0;
     b->steps = P.steps && hipGetDevice(&b->device) == hipSuccess && b->device < kMaxStepDevices &&
+               hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, b->device) == hipSuccess &&
                steps1d_fits(P.nwork, P.waves, P.shape);
     if (b->steps) {
         // (a copy like the tables above, finished when it returns: a memset on
@@ -738,12 +805,13 @@ int batch_step(fpic_batch *b, int64_t nsteps)
             return rc;
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (left > 0 && hipStreamIsCapturing(b->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
-            for (; left > 0; left -= kStepsPerLaunch) {
+            for (; left > 0 && steps_reserve(b); left -= kStepsPerLaunch) {
                 rc = run_steps(b, b->ddesc, 0, 0, (int)std::min<int64_t>(left, kStepsPerLaunch));
                 if (rc)
                     return rc;
             }
-            return FPIC_OK;
+            if (left <= 0)
+                return FPIC_OK;
         }
         (void)hipGetLastError();
         rc = ensure_graphs(b);
@@ -846,15 +914,13 @@ void fpic_batch_destroy(fpic_batch *b)
         (void)hipGraphExecDestroy(g.second);
     for (auto &g : b->adj.reverse)
         (void)hipGraphExecDestroy(g.second);
-    if (b->steps) {
+    if (b->done) {
+        // (counts until its latest launch has ended)
+        (void)hipEventSynchronize(b->done);
         std::lock_guard<std::mutex> lock(g_steps_mu);
-        if (g_steps_last[b->device] == b) {
-            (void)hipEventSynchronize(b->done);
-            g_steps_last[b->device] = nullptr;
-        }
-    }
-    if (b->done)
+        steps_unlist(b);
         (void)hipEventDestroy(b->done);
+    }
     if (b->g1)
         (void)hipGraphExecDestroy(b->g1);
     if (b->gK)
@@ -1356,10 +1422,11 @@ int fpic_adjoint_backward(fpic_ctx *c, const double *dLdy_end, double *dLdy0, do
         HIPCHECK(launch_stage1d(M_DEPOSIT, b->dwork + off, n, F, P.waves, P.max_dpw, P.shape, P.nt, 0, s));
         HIPCHECK(launch_reduce1d(b->dred + roff, rn, F, 0, nullptr, 0, s));
         hipGraphExec_t g = nullptr;
-        int rc = b->steps ? run_steps(b, F, 1, 1, len) : adj_graph(b, false, len, &g);
+        const bool whole = b->steps && steps_reserve(b);
+        int rc = whole ? run_steps(b, F, 1, 1, len) : adj_graph(b, false, len, &g);
         if (rc)
             return rc;
-        if (!b->steps)
+        if (!whole)
             HIPCHECK(hipGraphLaunch(g, s));
         // sweep the segment backwards
         HIPCHECK(launch_set_step(F, 0, 1, n0 + len - 1, s));

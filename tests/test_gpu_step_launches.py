@@ -91,3 +91,83 @@ def test_given_up_wait_in_a_batch():
     for call in (b.sync, b.step, b.flavor_totals, lambda: b.get_state(1), lambda: b.set_state(1, state(ws[1]))):
         with pytest.raises(FpicError):
             call()
+
+
+def independent_streams():
+    """Two streams, the second of which goes on while the first is busy (the
+    runtime maps streams to a few hardware queues)."""
+    a, x = torch.cuda.Stream(), torch.zeros(1, device="cuda")
+    for b in [torch.cuda.Stream() for _ in range(8)]:
+        torch.cuda.synchronize()
+        with torch.cuda.stream(a):
+            torch.cuda._sleep(200_000_000)
+            busy = torch.cuda.Event()
+            busy.record()
+        with torch.cuda.stream(b):
+            x.add_(1)
+        b.synchronize()
+        if not busy.query():
+            return a, b
+    pytest.skip("no two streams that run side by side")
+
+
+@pytest.mark.parametrize("nz,ndir", [(32, 26), (200, 92), (2048, 64)])
+def test_streams_do_not_wait_for_one_another(nz, ndir):
+    """A box whose stream waits behind other work holds up no box on another
+    stream, whether both fit the chip together (32 x 26: 4 workgroups, 200 x
+    92: 48) or not (2048 x 64: 256)."""
+    a, b = independent_streams()
+    w = box(nz, ndir, 1)
+    sims = []
+    for q in (a, b):
+        with torch.cuda.stream(q):
+            sims.append(Sim.from_workload(w))
+            sims[-1].set_state(state(w))
+    for s in sims:
+        s.step(1)
+        s.sync()
+    with torch.cuda.stream(a):
+        torch.cuda._sleep(2_000_000_000)
+        sims[0].step(3)
+        sims[0].step(3)
+        busy = torch.cuda.Event()
+        busy.record()
+    sims[1].step(3)
+    sims[1].step(3)
+    sims[1].sync()
+    assert not busy.query()
+    sims[0].sync()
+    sims[1].step(2)
+    sims[0].step(2)
+    ref = reference(w, 9)
+    for s in sims:
+        s.sync()
+        assert torch.equal(s.get_state(), ref)
+        torch.cuda.synchronize()
+
+
+def test_adjoint_beside_another_stream():
+    """The recomputation of a segment beside a launch that takes the whole
+    chip: gradients bit for bit those of a context alone."""
+    a, b = independent_streams()
+    w, wide = box(130, 24, 1), box(2048, 64, 1)
+    g = torch.from_numpy(state(w)).cuda()
+
+    def gradients(q):
+        with torch.cuda.stream(q):
+            s = Sim.from_workload(w)
+            s.set_state(state(w))
+            s.adjoint_forward(5, 2)
+            return s.adjoint_backward(g)
+
+    torch.cuda.synchronize()
+    alone = gradients(b)
+    with torch.cuda.stream(a):
+        s = Sim.from_workload(wide)
+        s.set_state(state(wide))
+        torch.cuda._sleep(1_000_000_000)
+        s.step(2)
+    beside = gradients(b)
+    torch.cuda.synchronize()
+    assert torch.equal(alone[0], beside[0])
+    assert (alone[1] == beside[1]).all() and (alone[2] == beside[2]).all()
