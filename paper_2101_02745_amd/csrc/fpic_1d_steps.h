@@ -37,11 +37,16 @@ typedef const __attribute__((address_space(4))) SimDesc cSimDesc;
 
 typedef __attribute__((address_space(1))) unsigned guint;
 
-// A wait at a barrier is given up: no result of the context is valid any more.
-__device__ __forceinline__ void give_up(const GridBar &b)
+// Waits until counter c has reached target; false if the wait was given up.
+__device__ __forceinline__ bool reached(const GridBar &b, guint *c, unsigned target)
 {
-    __hip_atomic_store((guint *)(b.cnt + kBarBad), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(b.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const unsigned long long t0 = wall_clock64();
+    while ((int)(__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
+        if (wall_clock64() - t0 > b.bar_ticks)
+            return false;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return true;
 }
 
 // Barrier number gen (from 1) over the grid; false if the wait was given up.
@@ -57,17 +62,28 @@ __device__ __forceinline__ bool grid_sync(const GridBar &b, unsigned gen, int *s
         guint *top = (guint *)b.cnt, *mine = (guint *)(b.cnt + kBarStride * (1 + grp));
         if (__hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gen * size)
             __hip_atomic_fetch_add(top, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int ok = 1;
-        const unsigned long long t0 = wall_clock64();
-        while ((int)(__hip_atomic_load(top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - gen * ngrp) < 0) {
-            if (wall_clock64() - t0 > b.bar_ticks) {
-                give_up(b);
-                ok = 0;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        *sflag = ok;
+        *sflag = reached(b, top, gen * ngrp);
+    }
+    __syncthreads();
+    return *sflag != 0;
+}
+
+// The workgroups that do a launch's work: this one's number among them (size
+// or more: it has nothing to do).
+struct Team {
+    unsigned rank, size;
+};
+
+// The same over a team that is not the whole grid: barrier number gen (from 1)
+// of the launch.
+__device__ __forceinline__ bool team_sync(const GridBar &b, const Team &t, unsigned gen, int *sflag)
+{
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        guint *c = (guint *)(b.cnt + kBarTeam);
+        __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *sflag = reached(b, c, gen * t.size);
     }
     __syncthreads();
     return *sflag != 0;
@@ -274,30 +290,34 @@ __device__ __forceinline__ int64_t particle_at(const Item &I, const Shift &s)
     return (int64_t)I.d * I.nc + c;
 }
 
-// All steps of the work items [lo, hi).  Every wave has one direction of its
-// workgroup's tile, a particle a lane.  SERIAL false: one item, its particles
-// in registers: the state, the previous slope and the sum of the slopes so
-// far.  When the direction's anchor moves on by a cell from one stage to the
-// next, the wave moves its particles by one lane and passes the one at the
-// end to the neighbouring tile's wave through memory (xch, two buffers in
+// All steps of the launch's work items.  Every wave has one direction of its
+// workgroup's tile, a particle a lane.  SHARED false: one item a workgroup, its
+// particles in registers: the state, the previous slope and the sum of the
+// slopes so far.  When the direction's anchor moves on by a cell from one stage
+// to the next, the wave moves its particles by one lane and passes the one at
+// the end to the neighbouring tile's wave through memory (xch, two buffers in
 // turn); loading and storing them all in every stage, as the stage kernels
-// do, took 10.8 us a stage of the 32 x 26 box against 9.3.  SERIAL: one
-// workgroup takes every item in turn, stage by stage, with its particles in
-// memory (slopes in xch).  The four stages are one body (mode is uniform): a
-// body for each was 36 KB of code a stage, more than the instruction cache
-// holds for a step.
-template <int SH, bool SERIAL>
+// do, took 10.8 us a stage of the 32 x 26 box against 9.3.  SHARED: the team
+// takes the items in turn, stage by stage, with their particles in memory
+// (slopes in xch; a particle's next stage may be another workgroup's): two
+// steps of the 2048 x 64 box, with the host's wait, 700 us by 140 to 190 of its
+// 256 workgroups, against 436 by all.  The four stages are one body (mode is
+// uniform): a body for each was 36 KB of code a stage, more than the
+// instruction cache holds for a step.  False if a barrier's wait was given up.
+template <int SH, bool SHARED>
 __device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, const SimDesc *__restrict__ sims,
                                           int stride, int keep, int nsteps, const GridBar &bar, const Lds &L,
-                                          Columns &C, int *sflag, int lo, int hi, int wave, int lane, int nwaves)
+                                          Columns &C, int *sflag, const Team &team, int wave, int lane, int nwaves)
 {
     constexpr int GTC = gt_cells(SH), GTS = gt_stride(SH), NE = n_edges(SH);
     Item I;
     double Y[18], kp[18], ks[18];
     Shift sn;
     int move = 0;
+    const int lo = SHARED ? (int)team.rank : (int)blockIdx.x, hi = SHARED ? (int)gridDim.x : lo + 1;
+    const int inc = SHARED ? (int)team.size : 1;
     int64_t n0 = *((const cSimDesc *)(sims + work[lo].sim))->step;
-    if (!SERIAL) {
+    if (!SHARED) {
         set_item<SH>(I, work[lo], sims, L, C, wave, lane, nwaves);
         sn = anchor_shift(I.vz, n0, M_S1, I.ds->dt, I.ds->dz);
         const int64_t p = particle_at(I, sn), np = I.ds->np;
@@ -314,13 +334,13 @@ __device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, con
     for (int it = 0; it <= 4 * nsteps; ++it) {
         const bool last = it == 4 * nsteps, odd = it & 1;
         const int st = last ? nsteps - 1 : it >> 2, mode = (it & 3) + 1;
-        for (int item = lo; item < hi; ++item) {
-            if (SERIAL) {
+        for (int item = lo; item < hi; item += inc) {
+            if (SHARED) {
                 set_item<SH>(I, work[item], sims, L, C, wave, lane, nwaves);
                 n0 = *I.ds->step;
             }
             if (last && !I.first) {
-                if (SERIAL)
+                if (SHARED)
                     continue;
                 return true;
             }
@@ -328,22 +348,22 @@ __device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, con
             const int64_t n = n0 + (it >> 2), np = S.np;
             const double dt = S.dt, dz = S.dz;
             const int ntc = I.ntile * TILE, tile0 = I.tile * TILE;
-            if (SERIAL) {
+            if (SHARED) {
                 sn = anchor_shift(I.vz, n, mode, dt, dz);
                 const int64_t p = particle_at(I, sn);
                 const double *Yp = S.Y, *kx = S.xch;
 #pragma unroll
                 for (int k = 0; k < 18; k++) {
-                    Y[k] = I.active ? gld(Yp + k * np + p) : 0.0;
-                    kp[k] = I.active && mode != M_S1 ? gld(kx + k * np + p) : 0.0;
-                    ks[k] = I.active && mode != M_S1 ? gld(kx + (18 + k) * np + p) : 0.0;
+                    Y[k] = I.active ? xld<true>(Yp + k * np + p) : 0.0;
+                    kp[k] = I.active && mode != M_S1 ? xld<true>(kx + k * np + p) : 0.0;
+                    ks[k] = I.active && mode != M_S1 ? xld<true>(kx + (18 + k) * np + p) : 0.0;
                 }
             }
             const Shift sc = shift_of(I.vz, stage_time(n, dt, mode == M_S1 ? 0.0 : (mode == M_S4 ? 1.0 : 0.5)), dz);
             const int delta = max(-1, min(1, (int)(sn.i - sc.i)));
             // the particle that comes in from the next tile, a real a lane;
             // used after the tile has formed
-            const bool moves = !SERIAL && move != 0 && I.has && !last;
+            const bool moves = !SHARED && move != 0 && I.has && !last;
             double in = 0.0;
             if (moves && I.ntile > 1 && lane < kPart) {
                 const int nb = move > 0 ? (I.tile == 0 ? I.ntile - 1 : I.tile - 1)
@@ -380,7 +400,7 @@ __device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, con
             }
             if (last) {
                 // the boxes' step counters: every workgroup has read them
-                if (!SERIAL && I.tile == 0 && threadIdx.x == 0)
+                if (!SHARED && I.tile == 0 && threadIdx.x == 0)
                     *I.ds->step = n0 + nsteps;
                 __syncthreads();
                 continue;
@@ -422,22 +442,22 @@ __device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, con
                             ks[k] = mode == M_S1 ? kp[k] : ks[k] + 2.0 * kp[k];
                         }
                     }
-                    if (SERIAL || keep || it == 4 * nsteps - 1) {
+                    if (SHARED || keep || it == 4 * nsteps - 1) {
                         const int64_t p = particle_at(I, sn);
                         if (mode == M_S4) {
                             double *out = S.Yout;
 #pragma unroll
                             for (int k = 0; k < 18; k++)
-                                gst(out + k * np + p, Y[k]);
+                                xst<SHARED>(out + k * np + p, Y[k]);
                         } else if (keep) {
                             store_slope(mode == M_S1 ? S.K1 : (mode == M_S2 ? S.K2 : S.K3), np, p, kp);
                         }
-                        if (SERIAL) {
+                        if (SHARED) {
                             double *kx = S.xch;
 #pragma unroll
                             for (int k = 0; k < 18; k++) {
-                                gst(kx + k * np + p, kp[k]);
-                                gst(kx + (18 + k) * np + p, ks[k]);
+                                xst<true>(kx + k * np + p, kp[k]);
+                                xst<true>(kx + (18 + k) * np + p, ks[k]);
                             }
                         }
                     }
@@ -455,7 +475,7 @@ __device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, con
                 for (int k = 0; k < 9; k++)
                     L.xc[(wave * 9 + k) * TILE + lane] = xc[k];
             }
-            if (!SERIAL) {
+            if (!SHARED) {
                 // the next stage's anchor; the particle that leaves the tile
                 // with it
                 const int nmode = (mode & 3) + 1;
@@ -521,25 +541,29 @@ __device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, con
                     xst<true>(edge + (((size_t)I.group * NG + r) * NE + e) * I.ntile + I.tile, t);
                 }
             }
-            if (SERIAL)
+            if (SHARED)
                 __syncthreads();  // the next item overwrites the LDS
         }
-        if (SERIAL) {
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-            __syncthreads();
-        } else if (!last && !grid_sync(bar, bar.gen + (unsigned)it + 1u, sflag)) {
+        // (a team waits after the last turn too: its first workgroup then
+        // writes the step counters)
+        if (SHARED ? !team_sync(bar, team, (unsigned)it + 1u, sflag)
+                   : !last && !grid_sync(bar, bar.gen + (unsigned)it + 1u, sflag))
             return false;
-        }
     }
     return true;
 }
 
-// After a wait that was given up: NaN in every state that the launch was to
-// return (by each workgroup that gives up, the last of them last), so that
-// what is read from the context before the host has looked at the failure
-// word cannot pass for a result.
-__device__ __forceinline__ void spoil(const WorkItem *__restrict__ work, const SimDesc *__restrict__ sims, int end)
+// After a wait that was given up: the failure words, then NaN in every state
+// that the launch was to return (by each workgroup that gives up, the last of
+// them last), so that what is read from the context before the host has looked
+// at its word cannot pass for a result.
+__device__ __forceinline__ void give_up(const GridBar &b, const WorkItem *__restrict__ work,
+                                        const SimDesc *__restrict__ sims, int end)
 {
+    if (threadIdx.x == 0) {
+        __hip_atomic_store((guint *)(b.cnt + kBarBad), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(b.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     for (int q = 0; q < (int)gridDim.x; ++q) {
         if (work[q].tile != 0 || work[q].group != 0)
             continue;
@@ -550,52 +574,60 @@ __device__ __forceinline__ void spoil(const WorkItem *__restrict__ work, const S
     }
 }
 
-// Whether the launch's workgroups run together: 1, every workgroup is
-// resident; 0, they are not and another workgroup does the work (or an earlier
-// launch has given up a wait, and there is nothing to do); 2, they are not and
-// this one does it all.
+// The workgroups that do the launch's work: all of them, once every one is
+// resident, or those that are when a wait for that has lasted arrive_ticks.
 //
-// Every workgroup counts itself in; the last one decides for 1.  One that has
-// waited kArriveTicks for that decides against it (the first decision holds):
-// the others, waiting or yet to start, then end at once, so that no wait
-// depends on a workgroup that cannot start.  Launches of this process that run
-// at the same time fit the chip together (steps_reserve on the host), so that
-// this is for other kernels that hold CUs for as long.
-__device__ __forceinline__ int run_together(const GridBar &b, int *sflag)
+// Every workgroup counts itself in, which numbers it.  The last one decides for
+// the whole grid.  One that has waited arrive_ticks decides for those that have
+// counted in by then (the first decision holds): the others, when they start,
+// end at once, so that no wait depends on a workgroup that cannot start.
+// Launches of this process that run at the same time fit the chip together
+// (steps_reserve on the host), so that this is for other kernels that hold CUs
+// for as long.  The decision is one word: the launch's number, then the team's
+// size (kDeciding: being made).  After a wait that an earlier launch has given
+// up, nobody does anything.
+constexpr unsigned kSizeBits = 10, kDeciding = (1u << kSizeBits) - 1;
+static_assert(kMaxStepWgs < kDeciding, "a team's size fits its bits");
+
+__device__ __forceinline__ Team team_of(const GridBar &b, int *sflag)
 {
     if (threadIdx.x == 0) {
         guint *arrive = (guint *)(b.cnt + kBarArrive), *mode = (guint *)(b.cnt + kBarMode);
-        const unsigned go = 2u * b.launch + 1u, alone = go + 1u;
-        const unsigned target = b.launch * gridDim.x + gridDim.x;
-        // the first of the workgroups to call this decides
-        auto decide = [&](unsigned v) {
-            unsigned cur = __hip_atomic_load(mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            while (cur != go && cur != alone)
-                if (__hip_atomic_compare_exchange_strong(mode, &cur, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT))
-                    return true;
-            return false;
-        };
-        bool mine = false;
-        const unsigned bad = __hip_atomic_load((guint *)(b.cnt + kBarBad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == target)
-            decide(go);
-        const unsigned long long t0 = wall_clock64();
+        const unsigned tag = (b.launch + 1u) << kSizeBits, base = b.launch * gridDim.x;
+        // size of the team, 0: undecided (mode's value in cur)
         unsigned cur;
-        for (;;) {
+        auto decided = [&]() {
             cur = __hip_atomic_load(mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (cur == go || cur == alone)
-                break;
-            if (wall_clock64() - t0 >= b.arrive_ticks)
-                mine = decide(alone);
+            return (cur ^ tag) >> kSizeBits ? 0u : cur & kDeciding;
+        };
+        auto decide = [&](unsigned size) {
+            return __hip_atomic_compare_exchange_strong(mode, &cur, tag | size, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT);
+        };
+        const unsigned bad = __hip_atomic_load((guint *)(b.cnt + kBarBad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned rank = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
+        if (rank + 1u == gridDim.x && decided() == 0)
+            decide(gridDim.x);
+        const unsigned long long t0 = wall_clock64();
+        unsigned size;
+        while ((size = decided()) == 0 || size == kDeciding) {
+            if (size == 0 && wall_clock64() - t0 >= b.arrive_ticks && decide(kDeciding)) {
+                size = __hip_atomic_load(arrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
+                // the team's counter is clear before anyone counts on it
+                __hip_atomic_store((guint *)(b.cnt + kBarTeam), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __hip_atomic_store(mode, tag | size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
             __builtin_amdgcn_s_sleep(1);
         }
-        *sflag = bad ? 0 : (cur == go ? 1 : (mine ? 2 : 0));
+        sflag[0] = (int)rank;
+        sflag[1] = bad ? 0 : (int)size;
     }
     __syncthreads();
-    const int r = *sflag;
+    const Team t = {(unsigned)__builtin_amdgcn_readfirstlane(sflag[0]),
+                    (unsigned)__builtin_amdgcn_readfirstlane(sflag[1])};
     __syncthreads();
-    return r;
+    return t;
 }
 
 template <int SH>
@@ -604,7 +636,7 @@ steps1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ si
                int nsteps, GridBar bar)
 {
     extern __shared__ double smem[];
-    __shared__ int sflag;
+    __shared__ int sflag[2];
     __shared__ Columns C;
     const int lane = threadIdx.x & (TILE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / TILE);
@@ -616,26 +648,30 @@ steps1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ si
     L.eb = L.xc + nwaves * 9 * TILE;
     L.v = L.eb + nwaves * 9 * n_edges(SH);
     L.pass = L.v + nwaves * 4 + wave * kPart;  // this wave's
-    const int how = run_together(bar, &sflag);
-    if (how == 1) {
-        if (!all_steps<SH, false>(work, sims, stride, keep, nsteps, bar, L, C, &sflag, (int)blockIdx.x,
-                                  (int)blockIdx.x + 1, wave, lane, nwaves))
-            spoil(work, sims, (nsteps - 1) * stride);
-    } else if (how == 2) {
-        all_steps<SH, true>(work, sims, stride, keep, nsteps, bar, L, C, &sflag, 0, (int)gridDim.x, wave, lane,
-                            nwaves);
-        // the step counters, and the barriers that the next launch counts on
-        for (int q = threadIdx.x; q < (int)gridDim.x; q += blockDim.x)
-            if (work[q].tile == 0 && work[q].group == 0)
-                *sims[work[q].sim].step += nsteps;
-        const unsigned nwg = gridDim.x, ngrp = (nwg + kBarGroup - 1) / kBarGroup, nbar = 4u * nsteps;
-        for (unsigned g = threadIdx.x; g < ngrp; g += blockDim.x)
-            __hip_atomic_fetch_add((guint *)(bar.cnt + kBarStride * (1 + g)),
-                                   nbar * min((unsigned)kBarGroup, nwg - g * kBarGroup), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        if (threadIdx.x == 0)
-            __hip_atomic_fetch_add((guint *)bar.cnt, nbar * ngrp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const Team team = team_of(bar, sflag);
+    if (team.rank >= team.size)
+        return;
+    bool ok;
+    if (team.size == gridDim.x) {
+        ok = all_steps<SH, false>(work, sims, stride, keep, nsteps, bar, L, C, sflag, team, wave, lane, nwaves);
+    } else {
+        ok = all_steps<SH, true>(work, sims, stride, keep, nsteps, bar, L, C, sflag, team, wave, lane, nwaves);
+        if (ok && team.rank == 0) {
+            // the step counters, and the barriers that the next launch counts on
+            for (int q = threadIdx.x; q < (int)gridDim.x; q += blockDim.x)
+                if (work[q].tile == 0 && work[q].group == 0)
+                    *sims[work[q].sim].step += nsteps;
+            const unsigned nwg = gridDim.x, ngrp = (nwg + kBarGroup - 1) / kBarGroup, nbar = 4u * nsteps;
+            for (unsigned g = threadIdx.x; g < ngrp; g += blockDim.x)
+                __hip_atomic_fetch_add((guint *)(bar.cnt + kBarStride * (1 + g)),
+                                       nbar * min((unsigned)kBarGroup, nwg - g * kBarGroup), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            if (threadIdx.x == 0)
+                __hip_atomic_fetch_add((guint *)bar.cnt, nbar * ngrp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
+    if (!ok)
+        give_up(bar, work, sims, (nsteps - 1) * stride);
 }
 
 size_t steps1d_smem(int waves, int shape) { return lds_doubles(waves, shape) * sizeof(double); }

@@ -57,6 +57,7 @@ struct Carver {
 
 constexpr int kRedBlocks = 256;  // blocks of the diagnostic reductions
 constexpr int kFailed = 63;      // word of the pinned buffer: a step launch failed
+constexpr unsigned long long kArriveRule = ~0ull;
 // Contexts whose waves have one direction each, in at most one workgroup per
 // CU, run whole steps in one launch (fpic_1d_steps.h), if a tile has at most
 // kMaxStepGroups direction groups: every workgroup sums all groups' partials
@@ -333,9 +334,9 @@ struct fpic_batch {
     fpic_batch *steps_next = nullptr;  // (g_steps_head)
     bool launching = false;        // done not yet recorded for it
     int cus = 0, steps_held = 0;
-    // how long its workgroups wait to be resident together before one of them
-    // does all the work (in ticks of 10 ns; 1 s)
-    unsigned long long arrive_ticks = 100000000ull;
+    // how long its workgroups wait to be resident together before those that
+    // are do the work, in ticks of 10 ns (kArriveRule: see run_steps)
+    unsigned long long arrive_ticks = kArriveRule;
     unsigned long long bar_ticks = 2000000000ull;  // and at a barrier before it gives up (20 s)
     int device = 0;
     double cell_volume = 1.0;      // of simulation 0
@@ -473,11 +474,18 @@ bool steps_reserve(fpic_batch *b)
 }
 
 // nsteps steps of the descriptors ds + j stride in one launch, after
-// steps_reserve.
+// steps_reserve.  Its workgroups wait for one another at most 3 ms and about
+// as long as the steps take (100 us each): an idle chip takes 1 to 4 us, one
+// with other kernels on it as long as those run (products of 4096 x 4096
+// matrices 53 us, sweeps over 2 GB 2.1 ms), and another process' launch of
+// whole steps, which may hold a part of the chip while this one holds the rest
+// (two processes, 2048 x 64, once in 530 launches), would never make room.
 int run_steps(fpic_batch *b, const SimDesc *ds, int stride, int keep, int nsteps)
 {
     const Plan &P = b->plan;
-    const GridBar bar{reinterpret_cast<unsigned *>(b->ws + P.o_bar), b->launches, b->gen, b->arrive_ticks, b->bar_ticks,
+    const unsigned long long arrive =
+        b->arrive_ticks == kArriveRule ? 300000ull + 10000ull * (unsigned)nsteps : b->arrive_ticks;
+    const GridBar bar{reinterpret_cast<unsigned *>(b->ws + P.o_bar), b->launches, b->gen, arrive, b->bar_ticks,
                       reinterpret_cast<int *>(b->hbuf + kFailed)};
     hipError_t e = launch_steps1d(b->dwork, P.nwork, ds, stride, keep, P.waves, P.shape, nsteps, bar, b->stream);
     if (e == hipSuccess) {
@@ -494,7 +502,7 @@ int run_steps(fpic_batch *b, const SimDesc *ds, int stride, int keep, int nsteps
 }  // namespace
 
 // For tests: how long the workgroups of this context's step launches wait for
-// one another (0: one workgroup does all the work).
+// one another (0: the first ones do the work).
 int fpic::set_arrive_ticks(void *ctx, unsigned long long ticks)
 {
     fpic_ctx *c = static_cast<fpic_ctx *>(ctx);

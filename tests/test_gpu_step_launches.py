@@ -171,3 +171,59 @@ def test_adjoint_beside_another_stream():
     torch.cuda.synchronize()
     assert torch.equal(alone[0], beside[0])
     assert (alone[1] == beside[1]).all() and (alone[2] == beside[2]).all()
+
+
+# waits, in ticks of 10 ns, from none to about that of all workgroups of a
+# launch for one another: teams of few workgroups and of many
+WAITS = (0, 40, 80, 120, 160, 240, 10 ** 8)
+
+
+@pytest.mark.parametrize("nz,ndir,shape", [(2048, 64, 1), (777, 92, 2), (200, 92, 1), (16, 26, 2)])
+def test_teams(nz, ndir, shape):
+    """Where a launch's workgroups are not resident together in time, those
+    that are share the work: the same bits, launch after launch."""
+    w = box(nz, ndir, shape)
+    s = Sim.from_workload(w)
+    s.set_state(state(w), 3)
+    for ticks in WAITS:
+        set_waits(s, ticks, 2 * 10 ** 9)
+        s.step(2)
+    s.sync()
+    assert s.step_index() == 3 + 2 * len(WAITS)
+    assert torch.equal(s.get_state(), reference(w, 2 * len(WAITS), 3))
+
+
+def test_teams_in_a_batch():
+    """Boxes of other sizes and start steps, several of one workgroup."""
+    ws = [box(40, 24, 1), box(65, 26, 1, dz=0.2), box(130, 64, 1, dz=0.15, dt=0.05), box(16, 10, 1)]
+    b = Batch([HostConfig.from_workload(w) for w in ws])
+    for i, w in enumerate(ws):
+        b.set_state(i, state(w), 5 * i)
+    for ticks in WAITS:
+        set_waits(b, ticks, 2 * 10 ** 9)
+        b.step(3)
+    b.sync()
+    for i, w in enumerate(ws):
+        assert torch.equal(b.get_state(i), reference(w, 3 * len(WAITS), 5 * i))
+
+
+@pytest.mark.parametrize("nz,ndir,shape", [(130, 24, 1), (65, 26, 2), (512, 128, 1)])
+def test_teams_in_the_adjoint(nz, ndir, shape):
+    """The recomputation keeps every stage's grids and slopes for the reverse
+    sweep: the gradients of a team are those of the whole launch."""
+    w = box(nz, ndir, shape)
+    g = torch.from_numpy(state(w)).cuda()
+
+    def gradients(ticks):
+        s = Sim.from_workload(w)
+        s.set_state(state(w), 2)
+        s.adjoint_forward(5, 2)
+        if ticks is not None:
+            set_waits(s, ticks, 2 * 10 ** 9)
+        return s.adjoint_backward(g)
+
+    want = gradients(None)
+    for ticks in WAITS:
+        got = gradients(ticks)
+        assert torch.equal(got[0], want[0])
+        assert (got[1] == want[1]).all() and (got[2] == want[2]).all()
