@@ -161,21 +161,22 @@ bool is_1d(const fpic_config &c) { return c.ncell[0] == 1 && c.ncell[1] == 1; }
 // measured fastest in a sweep of 1-8 waves and 1-24 directions).  Workgroups
 // of 4 waves stage twice as many tiles per CU (219 us for the 2048 x 378 box)
 // and pay where their smaller granularity saves a round.  A single box gets
-// at most the workgroups (and partial sums) of 4 waves in about 1024 of them:
-// fpic_step_noalloc's fixed scratch, which takes the same shape, holds every
-// box up to the size its limit states.
+// at most the workgroups (and partial sums) of the caller's waves, or 4, in
+// about 1024 of them: fpic_step_noalloc's fixed scratch, which takes the same
+// shape, holds every box up to the size its limit states.
 void choose_shape(int nsim, const fpic_config *cfgs, int &waves, int &dpw)
 {
     constexpr int kCus = 256;
     const bool w_open = waves == 0, d_open = dpw == 0;
     int64_t most = INT64_MAX;
-    if (nsim == 1 && w_open && d_open) {
-        const int64_t ntile = (cfgs[0].ncell[2] + TILE - 1) / TILE, nd = cfgs[0].ndir;
-        const int64_t dpg = 4 * std::max<int64_t>(1, std::min<int64_t>(64, (ntile * nd + 4095) / 4096));
-        most = ntile * ((nd + dpg - 1) / dpg);
-    }
     double best = 1e300;
-    int bw = w_open ? 8 : waves, bd = d_open ? 32 : dpw;
+    int bw = w_open ? 4 : waves, bd = dpw;
+    if (d_open) {
+        const int64_t ntile = (cfgs[0].ncell[2] + TILE - 1) / TILE, nd = cfgs[0].ndir, target = 1024 * bw;
+        bd = (int)std::max<int64_t>(1, std::min<int64_t>(64, (ntile * nd + target - 1) / target));
+        if (nsim == 1)
+            most = ntile * ((nd + (int64_t)bw * bd - 1) / ((int64_t)bw * bd));
+    }
     for (int w : {8, 4}) {
         if (!w_open && w == 4)
             break;  // the caller's waves, once
