@@ -352,8 +352,9 @@ __device__ __forceinline__ Box block_box(const int f[3], bool active, const int 
 // their particle streams.
 // Returns false (workgroup-uniform) if the first cells of the workgroup's
 // particles spread over more than kMaxLow cells (the counters of the sort, in
-// the place of the accumulators; x, y, z in 12, 10, 10 bits); the caller then
-// adds particle by particle.
+// the place of the accumulators) or over more than 1024 in y or z (a first
+// cell is packed in 12, 10, 10 bits; so in a 1D box, along z, from 1025 on); the
+// caller then adds particle by particle.
 constexpr int kMaxLow = 4096, kMaxSlots = 128, kMaxMap = 1024;
 
 typedef unsigned uint2v __attribute__((ext_vector_type(2)));
