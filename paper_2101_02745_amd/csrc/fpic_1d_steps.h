@@ -12,7 +12,7 @@
 // are the same bit for bit.
 //
 // One barrier per stage: instead of a reduction pass, every workgroup sums
-// the direction groups' partials of the cells it interpolates from (67
+// the direction groups' partials of the cells it interpolates from (67 or 69
 // columns) straight into its LDS tile.  Partials go to two buffers in turn,
 // so a workgroup that runs ahead by one stage overwrites nothing that is
 // still read.
@@ -100,7 +100,12 @@ __device__ __forceinline__ int tile_cell(int cell, int nc)
 // share (9 components of 64 cells), every wave's edge buffer, the waves'
 // direction components, the particle a wave passes on.
 constexpr int kPart = 54;      // reals of a particle on its way: state, slope, sum of slopes
-constexpr int kMaxEdge = 24;   // edge entries of a tile's columns
+// Edge entries of a tile's columns, at most: every (source tile, slot) reaches
+// one cell, and the columns repeat a box of one tile of nc cells ceil(columns /
+// nc) times (with more tiles they hold fewer: at most 12).
+constexpr int kMaxEdge = 24;
+constexpr int edge_entries(int sh) { return n_edges(sh) * ((gt_cells(sh) + kMinStepCells - 1) / kMinStepCells); }
+static_assert(edge_entries(1) <= kMaxEdge && edge_entries(2) <= kMaxEdge, "no entry is left out");
 struct Lds {
     double *Gt, *Ge, *xc, *eb, *v, *pass;
 };
@@ -114,7 +119,7 @@ __host__ __device__ constexpr int lds_doubles(int nwaves, int sh)
 // they are added.
 struct Columns {
     int cell[gt_cells(2)];
-    int n;                    // edge entries, -1 if there are more than kMaxEdge
+    int n;                    // edge entries
     int col[kMaxEdge], src[kMaxEdge], slot[kMaxEdge];
 };
 
@@ -270,12 +275,10 @@ __device__ __forceinline__ void set_item(Item &I, const WorkItem &wi, const SimD
         for (int col = 0; col < GTC; ++col) {
             const int t = C.cell[col] / TILE;
             edge_sources(SH, I.nc, I.ntile, t, C.cell[col] - t * TILE, [&](int src, int e) {
-                if (n < kMaxEdge) {  // (always, with kMinStepCells cells or more)
-                    C.col[n] = col;
-                    C.src[n] = src;
-                    C.slot[n] = e;
-                    ++n;
-                }
+                C.col[n] = col;
+                C.src[n] = src;
+                C.slot[n] = e;
+                ++n;
             });
         }
         C.n = n;
