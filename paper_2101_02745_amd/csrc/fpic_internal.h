@@ -173,3 +173,5 @@ struct fpic_ctx;
 struct fpic_batch;
 extern "C" int fpic_test_step_waits(fpic_ctx *ctx, fpic_batch *batch, unsigned long long arrive_ticks,
                                     unsigned long long bar_ticks);
+// For tests: launches of whole steps so far, -1 if there are none to be made.
+extern "C" int fpic_test_step_launches(fpic_ctx *ctx, fpic_batch *batch);

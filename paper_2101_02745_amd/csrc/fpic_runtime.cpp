@@ -532,6 +532,12 @@ extern "C" int fpic_test_step_waits(fpic_ctx *ctx, fpic_batch *batch, unsigned l
     return FPIC_OK;
 }
 
+extern "C" int fpic_test_step_launches(fpic_ctx *ctx, fpic_batch *batch)
+{
+    fpic_batch *b = ctx ? ctx->b : batch;
+    return b && b->steps ? (int)b->launches : -1;
+}
+
 namespace {
 
 // The dispatcher hands workgroup b to XCD b % 8, and each XCD has its own

@@ -227,3 +227,74 @@ def test_teams_in_the_adjoint(nz, ndir, shape):
         got = gradients(ticks)
         assert torch.equal(got[0], want[0])
         assert (got[1] == want[1]).all() and (got[2] == want[2]).all()
+
+
+def launches(s):
+    """Launches of whole steps so far, -1 for a context that makes none."""
+    f = _lib.load().fpic_test_step_launches
+    f.argtypes = [C.c_void_p, C.c_void_p]
+    return f(getattr(s, "ctx", None), getattr(s, "b", None))
+
+
+@pytest.mark.parametrize("nz,ndir,shape,whole", [(15, 8, 1, False), (16, 8, 2, True), (32, 26, 1, True),
+                                                 (777, 92, 2, True), (2048, 64, 1, True), (2049, 64, 1, False),
+                                                 (100, 192, 1, True), (100, 194, 1, False)])
+def test_which_boxes_take_whole_steps(nz, ndir, shape, whole):
+    """Both sides of the rule: at least 16 cells, at most 256 workgroups and 24
+    direction groups, one direction a wave, every slope stored by choice."""
+    w = box(nz, ndir, shape)
+    s = Sim.from_workload(w)
+    s.set_state(state(w))
+    s.step(3)
+    s.step(600)
+    assert launches(s) == (3 if whole else -1)    # 3, 512 and 88 steps
+    for tune in (dict(fused=2), dict(waves=8, dirs_per_wave=2)):
+        assert launches(Sim.from_workload(w, tuning=tune)) == -1
+
+
+def test_batches_and_the_adjoint_take_whole_steps():
+    ws = [box(40, 24, 1), box(65, 26, 1)]
+    b = Batch([HostConfig.from_workload(w) for w in ws])
+    for i, w in enumerate(ws):
+        b.set_state(i, state(w))
+    b.step(4)
+    assert launches(b) == 1
+    w = box(130, 24, 1)
+    s = Sim.from_workload(w)
+    s.set_state(state(w))
+    s.adjoint_forward(5, 2)
+    assert launches(s) == 3
+    s.adjoint_backward(state(w))
+    assert launches(s) == 6
+
+
+def test_steps_while_the_stream_is_captured():
+    """A box that runs whole steps does under capture what one launch per stage
+    does, and goes on with whole steps afterwards."""
+    w = box(65, 26, 2)
+    q = torch.cuda.Stream()
+    got = []
+    for tune in (None, dict(fused=2)):
+        with torch.cuda.stream(q):
+            s = Sim.from_workload(w, tuning=tune)
+            s.set_state(state(w), 4)
+            s.step(1)
+            s.sync()
+        before = launches(s)
+        g = torch.cuda.CUDAGraph()
+        x = torch.zeros(4, device="cuda")
+        with torch.cuda.graph(g, stream=q):
+            x.add_(1.0)
+            s.step(11)
+        assert launches(s) == before
+        for _ in range(3):
+            g.replay()
+            torch.cuda.synchronize()
+        s.step(2)
+        s.sync()
+        assert launches(s) == (before + 1 if tune is None else -1)
+        got.append((s.step_index(), s.get_state()))
+        torch.cuda.synchronize()
+    assert got[0][0] == got[1][0]
+    assert torch.equal(got[0][1], got[1][1])
+    assert torch.equal(got[0][1], reference(w, got[0][0] - 4, 4))
