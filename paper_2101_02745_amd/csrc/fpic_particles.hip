@@ -101,7 +101,11 @@ struct PDesc {
     double *G0, *G1, *G2;  // [ncell][4 NXT] stage grids
     int64_t *step;
     int32_t *cnt, *cur;  // [ncell] sort counters
-    long long *GL;       // deposit limbs: per cell the hi limbs of its components, then the lo limbs
+    // deposit limbs.  Stages: per cell the hi limbs of its components, then the
+    // lo limbs (deposit_runs adds a cell at a time).  Moments: [2][NG][ncell],
+    // hi plane, then lo plane (their lanes add one component of neighbouring
+    // cells at a time; all zero between two deposits)
+    long long *GL;
     double qs, qi;       // 2^S and 2^-S: the fixed-point scale of the deposits
 };
 
@@ -181,7 +185,7 @@ __device__ __forceinline__ void lds_add_limbs(long long *hi_p, long long *lo_p, 
     atomicAdd(reinterpret_cast<unsigned long long *>(lo_p), lo);
 }
 
-__device__ __forceinline__ void global_add_limbs(long long *GL, int plane, int64_t q, double m, double x)
+__device__ __forceinline__ void global_add_limbs(long long *GL, int64_t plane, int64_t q, double m, double x)
 {
     unsigned long long hi, lo;
     product_limbs(m, x, hi, lo);
@@ -990,12 +994,27 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
     // instruction's lanes target different corners
     const int rot = lane % NCORNER;
 
-    // grid index of the moment kernels' box cell l
-    auto box_cell = [&](int l) {
-        const int cz = wrap_int(db.ref[2] + db.lo[2] + (D3 ? l / (sx * sy) : l), nz);
-        const int cy = D3 ? wrap_int(db.ref[1] + db.lo[1] + (l / sx) % sy, ny) : 0;
-        const int cx = D3 ? wrap_int(db.ref[0] + db.lo[0] + l % sx, nx) : 0;
-        return ((int64_t)cz * ny + cy) * nx + cx;
+    // f(c, l, cell) for the moment kernels' components c < ncomp of every box
+    // cell l (grid index cell): in 3D by BLK / cells threads a cell, each of
+    // which forms its grid index once
+    auto box_entries = [&](int cells, int ncomp, auto f) {
+        if (D3) {
+            const int per = cells < BLK ? BLK / cells : 1;
+            for (int t = threadIdx.x; t < per * cells; t += BLK) {
+                const int l = t % cells;
+                const int cz = wrap_int(db.ref[2] + db.lo[2] + l / (sx * sy), nz);
+                const int cy = wrap_int(db.ref[1] + db.lo[1] + (l / sx) % sy, ny);
+                const int cx = wrap_int(db.ref[0] + db.lo[0] + l % sx, nx);
+                const int64_t cell = ((int64_t)cz * ny + cy) * nx + cx;
+                for (int c = t / cells; c < ncomp; c += per)
+                    f(c, l, cell);
+            }
+        } else {
+            for (int q = threadIdx.x; q < ncomp * cells; q += BLK) {
+                const int c = q / cells, l = q - c * cells;
+                f(c, l, (int64_t)wrap_int(db.ref[2] + db.lo[2] + l, nz));
+            }
+        }
     };
     if (!FULL && deposit_runs<SH, D3, EXACT>(S, db, o, active, Xd, dw, vx, vy, vz, acc, Gout)) {
         // the stages' deposit
@@ -1066,10 +1085,9 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
                 __syncthreads();
                 // integer sums, so the order in which the atomics land does
                 // not matter
-                for (int q = threadIdx.x; q < half; q += BLK) {
-                    const int c = q / cells, l = q - c * cells;
-                    flush_limbs(lacc, R, cstride, half, q, S.GL, box_cell(l) * 2 * NGC + g0 * NCS + c, NGC);
-                }
+                box_entries(cells, NCS * gpp, [&](int c, int l, int64_t cell) {
+                    flush_limbs(lacc, R, cstride, half, c * cells + l, S.GL, (g0 * NCS + c) * nc + cell, NG * nc);
+                });
                 __syncthreads();  // the next pass clears the accumulators
             }
         } else if (active) {
@@ -1084,13 +1102,15 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
                 const int cz = wrap_int(df[2] + bz, nz);
                 const int cy = D3 ? wrap_int(df[1] + by, ny) : 0;
                 const int cx = D3 ? wrap_int(df[0] + bx, nx) : 0;
-                const int64_t g = ((int64_t)cz * ny + cy) * nx + cx;
+                const int64_t cell = ((int64_t)cz * ny + cy) * nx + cx;
+                const int64_t cs = FULL ? nc : 1, plane = FULL ? NG * nc : NGC;
+                long long *g = S.GL + (FULL ? cell : cell * 2 * NGC);
 #pragma unroll 1
                 for (int k = 0; k < NCS; k++) {
-                    global_add_limbs(S.GL, NGC, g * 2 * NGC + k, w, Xd[k]);
-                    global_add_limbs(S.GL, NGC, g * 2 * NGC + NCS + k, w, vx * Xd[k]);
-                    global_add_limbs(S.GL, NGC, g * 2 * NGC + 2 * NCS + k, w, vy * Xd[k]);
-                    global_add_limbs(S.GL, NGC, g * 2 * NGC + 3 * NCS + k, w, vz * Xd[k]);
+                    global_add_limbs(g, plane, k * cs, w, Xd[k]);
+                    global_add_limbs(g, plane, (NCS + k) * cs, w, vx * Xd[k]);
+                    global_add_limbs(g, plane, (2 * NCS + k) * cs, w, vy * Xd[k]);
+                    global_add_limbs(g, plane, (3 * NCS + k) * cs, w, vz * Xd[k]);
                 }
             }
         }
@@ -1127,14 +1147,13 @@ pstage_kernel(const PDesc *__restrict__ dp, double *outG)
             }
         }
         __syncthreads();
-        for (int q = threadIdx.x; q < NGC * cells; q += BLK) {
-            const int comp = q / cells, l = q - comp * cells;
+        box_entries(cells, NGC, [&](int c, int l, int64_t cell) {
             double val = 0.0;
             for (int r = 0; r < R; r++)
-                val += acc[r * cstride + q];
+                val += acc[r * cstride + c * cells + l];
             if (val != 0.0)
-                gatomic_add(Gout + (int64_t)comp * nc + box_cell(l), val);
-        }
+                gatomic_add(Gout + c * nc + cell, val);
+        });
     } else if (active) {
 #pragma unroll
         for (int bz = 0; bz < SW; bz++)
@@ -1226,13 +1245,12 @@ __global__ void __launch_bounds__(256) finalize_kernel(const PDesc *__restrict__
     const int64_t len = (int64_t)NGC * S.ncell;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < len;
          q += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t cell = q / NGC;
-        const int comp = (int)(q - cell * NGC);
-        long long *a = S.GL + cell * 2 * NGC + comp;
         // (the stage grids per cell, the moments per component)
-        gst(G + (FULL ? comp * S.ncell + cell : q), from_limbs(a[0], a[NGC], S.qi));
+        const int64_t plane = FULL ? len : NGC;
+        long long *a = S.GL + (FULL ? q : q + q / NGC * NGC);
+        gst(G + q, from_limbs(a[0], a[plane], S.qi));
         a[0] = 0;
-        a[NGC] = 0;
+        a[plane] = 0;
     }
 }
 

@@ -86,7 +86,9 @@ def test_spread(case, exact):
     n, scale = len(pos), np.prod(ncell) / len(pos)
     dirs, st = w.dirs()[:n], w.state0()[:, :n]
     N, Nb = (a[:n] * scale for a in w.weights())
-    ref = ParticleProblem(ncell, dx, pos * dx, dirs, N, Nb, w.hvac(), w.dt, shape_order=order).step(st, 5)
+    P = ParticleProblem(ncell, dx, pos * dx, dirs, N, Nb, w.hvac(), w.dt, shape_order=order)
+    ref = P.step(st, 5)
+    mref = P.moments(ref, 5 * w.dt)
 
     def gpu(perm):
         sim = ParticleSim(ncell, dx, n, w.hvac(), w.dt, order, sort_every=2, exact=exact)
@@ -94,10 +96,18 @@ def test_spread(case, exact):
         sim.step(5)
         out = np.empty_like(ref)
         out[:, perm] = sim.get_state().cpu().numpy()
+        mom = sim.moments().cpu().numpy()
+        assert np.array_equal(mom, sim.moments().cpu().numpy()) or not exact
+        sim.step(1)     # the sums of the next stages start from zero again
+        last = np.empty_like(ref)
+        last[:, perm] = sim.get_state().cpu().numpy()
         sim.close()
-        return out
+        return out, mom, last
 
-    got = gpu(np.arange(n))
+    got, mom, last = gpu(np.arange(n))
     assert_parity(got, ref, what=f"{route} {ncell} order {order}")
+    assert np.abs(mom - mref.reshape(mom.shape)).max() <= 1e-12 * np.abs(mref).max()
+    assert_parity(last, P.step(ref, 1, 5), what=f"{route} {ncell} order {order}, step after the moments")
     if exact:
-        assert np.array_equal(got, gpu(np.random.RandomState(3).permutation(n)))
+        for a, b in zip((got, mom, last), gpu(np.random.RandomState(3).permutation(n))):
+            assert np.array_equal(a, b)
