@@ -820,13 +820,6 @@ static size_t smem1d_bytes(int waves, int max_dpw, int shape, int nslot)
     return (nslot * gslot + dir_doubles(waves, max_dpw, ne)) * sizeof(double);
 }
 
-size_t most_smem1d(int waves, int max_dpw, int shape)
-{
-    // stage 3 with both earlier slopes formed again; the adjoint's two tiles
-    return std::max(smem1d_bytes(waves, max_dpw, shape, 1) + sizeof(double) * NG * gt_stride(shape + 1) * 2,
-                    smem1d_bytes(waves, max_dpw, shape, 2));
-}
-
 template <int SH, bool NT, int RK>
 static hipError_t launch_stage1d_sh(int mode, const WorkItem *work, int nwork, const SimDesc *sims,
                                     int waves, int max_dpw, hipStream_t s)

@@ -686,7 +686,7 @@ bool steps1d_fits(int nwork, int waves, int shape)
     int dev = 0, cus = 0, per = 0;
     const size_t smem = steps1d_smem(waves, shape);
     const void *f = shape == 2 ? (const void *)steps1d_kernel<2> : (const void *)steps1d_kernel<1>;
-    const bool ok = nwork <= kMaxStepWgs && smem <= kLdsBytes && hipGetDevice(&dev) == hipSuccess &&
+    const bool ok = nwork <= kMaxStepWgs && smem <= 160 * 1024 && hipGetDevice(&dev) == hipSuccess &&
                     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
                     hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, f, waves * TILE, smem) == hipSuccess;
     (void)hipGetLastError();

@@ -156,10 +156,6 @@ hipError_t launch_totals(const SimDesc *sims, int sim, int nblk, double *out18, 
 hipError_t launch_check(const SimDesc *sims, int sim, int nblk, double *out2, hipStream_t s);
 hipError_t launch_fill_state(const SimDesc *sims, int sim, hipStream_t s);
 
-// LDS bytes of the 1D stage or adjoint workgroup that takes the most.
-constexpr size_t kLdsBytes = 160 * 1024;
-size_t most_smem1d(int waves, int max_dpw, int shape);
-
 int set_arrive_ticks(void *ctx, unsigned long long ticks);
 
 // Record msg as the calling thread's last error and return code.

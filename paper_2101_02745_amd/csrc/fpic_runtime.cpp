@@ -163,19 +163,22 @@ bool is_1d(const fpic_config &c) { return c.ncell[0] == 1 && c.ncell[1] == 1; }
 // and pay where their smaller granularity saves a round.  A single box gets
 // at most the workgroups (and partial sums) of the caller's waves, or 4, in
 // about 1024 of them: fpic_step_noalloc's fixed scratch, which takes the same
-// shape, holds every box up to the size its limit states.  With dirs_per_wave
-// given, 8 waves are taken only where their per-direction data fit the LDS (of
-// quadratic boxes, up to 50 directions a wave), as 4 waves' may up to twice as
-// many.
+// shape, holds every box up to the size its limit states.  With several
+// directions a wave given, 4 waves are taken: 8 make fewer workgroups of longer
+// waves (us per step, 4 against 8: 200 x 92 with 4 directions 170, 230; 512 x
+// 128 with 4 117, 139, with 12 236, 291; 2048 x 378 with 12 268, 308, with 4
+// 293, 284), and from 51 directions a wave on those of a quadratic box pass the
+// LDS.
 void choose_shape(int nsim, const fpic_config *cfgs, int &waves, int &dpw)
 {
     constexpr int kCus = 256;
     const bool w_open = waves == 0, d_open = dpw == 0;
     int64_t most = INT64_MAX;
+    if (dpw > 1) {
+        waves = w_open ? 4 : waves;
+        return;
+    }
     double best = 1e300;
-    int nd_max = 1;
-    for (int i = 0; i < nsim; ++i)
-        nd_max = std::max(nd_max, (int)cfgs[i].ndir);
     int bw = w_open ? 4 : waves, bd = dpw;
     if (d_open) {
         const int64_t ntile = (cfgs[0].ncell[2] + TILE - 1) / TILE, nd = cfgs[0].ndir, target = 1024 * bw;
@@ -191,8 +194,6 @@ void choose_shape(int nsim, const fpic_config *cfgs, int &waves, int &dpw)
             if (!d_open && d > 1)
                 break;  // the caller's dpw, once
             const int dp = d_open ? d : dpw;
-            if (w_open && most_smem1d(wv, std::min(dp, nd_max), cfgs[0].shape_order) > kLdsBytes)
-                continue;
             int64_t wg = 0;
             for (int i = 0; i < nsim; ++i) {
                 const int64_t dpg = (int64_t)wv * std::min(dp, cfgs[i].ndir);

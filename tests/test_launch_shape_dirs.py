@@ -1,5 +1,5 @@
-"""dirs_per_wave given and waves left open: 8 waves only where the kernels' LDS
-holds their per-direction data, 4 otherwise."""
+"""dirs_per_wave given and waves left open: 4 waves, whose LDS holds twice the
+directions of 8."""
 import numpy as np
 import pytest
 
@@ -8,28 +8,13 @@ from oracle import Problem
 from test_gpu_steps_1d import box, state
 from test_launch_shape_cpu import nbytes
 
-LDS = 160 * 1024
-
-
-def lds(waves, dpw, shape):
-    """LDS bytes of a stage 3 that forms both earlier slopes again, and of an
-    adjoint kernel."""
-    ne = 3 if shape == 2 else 1
-    cells = 64 + 2 * shape + 2
-    slot = max(36 * cells, 36 * 64 + waves * 36 * ne)
-    dirs = waves * dpw * (9 * ne + 3)
-    return 8 * max(slot + dirs + 2 * 36 * (cells + 2), 2 * slot + dirs)
-
 
 @pytest.mark.parametrize("shape", [1, 2])
-@pytest.mark.parametrize("dpw", [16, 32, 48, 49, 50, 51, 52, 64, 96, 120, 128, 150, 200, 256])
-def test_waves_fit_the_lds(shape, dpw):
-    nz, ndir = 64, 8 * 256
-    got = nbytes(nz, ndir, shape, dict(dirs_per_wave=dpw))
-    if lds(8, dpw, shape) > LDS:
-        assert got == nbytes(nz, ndir, shape, dict(waves=4, dirs_per_wave=dpw))
-    else:
-        assert got == nbytes(nz, ndir, shape, dict(waves=8, dirs_per_wave=dpw))
+@pytest.mark.parametrize("nz,ndir", [(64, 2048), (200, 92), (2048, 378)])
+@pytest.mark.parametrize("dpw", [2, 4, 12, 51, 64, 128, 150, 256])
+def test_four_waves(nz, ndir, shape, dpw):
+    assert nbytes(nz, ndir, shape, dict(dirs_per_wave=dpw)) == \
+        nbytes(nz, ndir, shape, dict(waves=4, dirs_per_wave=dpw))
 
 
 @pytest.mark.gpu
