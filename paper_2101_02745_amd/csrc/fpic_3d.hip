@@ -632,20 +632,30 @@ deposit3d_kernel(const Desc3 *__restrict__ dp, int half_steps, int out_buf)
 // 24 quadratic 2.04 -> 2.02 ms.
 static bool streams(const Desc3 &h) { return h.n[0] <= W && h.n[0] % 16 == 0; }
 
-// Waves that share a destination row in the deposits: four up to 1.25 times the
-// rows that the chip holds with one wave each (its registers allow 8 waves of
-// the linear kernel and 12 of the quadratic one on each of 256 CUs), above that
-// one.  Per step, one wave a row against four: 12 x 10 x 14 cells x 50
-// directions quadratic (140 rows) 1010 -> 456 us, 70 x 8 x 8 x 12 (128) 161 ->
-// 106, 50 x 44 x 36 x 24 quadratic (1584) 1885 -> 1839, 100 x 36 x 30 x 24 (2160)
-// 1872 -> 1814, 100 x 40 x 40 x 24 quadratic (3200) 3369 -> 3275; but 100 x 50 x
-// 30 x 24 (3000) 2435 and 2455, 150 x 40 x 32 x 24 (3840) 3037 and 3060, 64^3 x 92
-// quadratic (4096) 14.86 and 15.37 ms.
-static int deposit_slices(const Desc3 &h)
+// Waves that share a destination row in the deposits (full: of the moments'
+// nine components): four up to 1.25 times the rows that the chip holds with one
+// wave each, above that one.  With one wave a row the registers allow 12 waves
+// of the quadratic stage kernel and 8 of the others on each of 256 CUs (with
+// four waves a row, 8 of each).  Per step, one wave a row against four: 12 x 10
+// x 14 cells x 50 directions quadratic (140 rows) 1010 -> 456 us, 70 x 8 x 8 x
+// 12 (128) 161 -> 106, 50 x 44 x 36 x 24 quadratic (1584) 1908 -> 1849, 32 x 48
+// x 48 x 92 (2304) 4459 -> 4205, quadratic 6497 -> 6116, 128 x 36 x 32 x 92
+// quadratic (3456) 11786 -> 11612; but 150 x 40 x 32 x 24 (3840) 3037 and 3060,
+// 64^3 x 92 quadratic (4096) 14.86 and 15.37 ms.  One wave also where the rows
+// just fill the chip once (32 x 44 x 44 x 92, 1936 rows, 3752 and 3778 us; 128
+// x 32 x 32 x 92 quadratic, 3072, 10252 and 10612, its moments 2745 and 2871),
+// and with few directions, of which four waves have hardly one each, unless the
+// rows are very few (moments of 32 x 44 x 44 x 4, 93 and 109 us; 20^3 x 4, 400
+// rows, 71 and 63).
+static int deposit_slices(const Desc3 &h, bool full)
 {
     const bool quad = h.shape == 2;
     const int64_t rows = (int64_t)h.n[1] * h.n[2] * xsegs(h.n[0], quad ? W - 2 : W - 1);
-    const int64_t held = 256 * (quad ? 12 : 8);
+    const int64_t held = 256 * (quad && !full ? 12 : 8);
+    if (h.ndir < 8 && 4 * rows > held)
+        return 1;
+    if (10 * rows > 9 * held && rows <= held)
+        return 1;
     return 4 * rows <= 5 * held ? 4 : 1;
 }
 
@@ -1841,7 +1851,7 @@ static void launch_deposit_ds(const Ctx3D *c, const Desc3 *dd, int half_steps, i
 static void launch_deposit(const Ctx3D *c, const Desc3 *dd, int half_steps, int out_buf, hipStream_t s,
                            bool full = false)
 {
-    if (deposit_slices(c->h) == 4)
+    if (deposit_slices(c->h, full) == 4)
         launch_deposit_ds<4>(c, dd, half_steps, out_buf, s, full);
     else
         launch_deposit_ds<1>(c, dd, half_steps, out_buf, s, full);
