@@ -99,7 +99,9 @@ typedef struct fpic_tuning {
                                 which pays when one box's arrays overflow the
                                 256 MB Infinity Cache; 0 chooses by size
                                 (streaming for a single box of 176 to 320 MB
-                                of state).  3D boxes choose by row length. */
+                                of state).  3D boxes: the fused kernels
+                                always stream, the separate ones for rows of
+                                whole cache lines. */
     int32_t fused;           /* 3D boxes with the linear shape: 0 or 1 one
                                 kernel per stage that also deposits, through
                                 per-workgroup partial rows and a small

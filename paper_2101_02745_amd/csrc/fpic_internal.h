@@ -114,14 +114,15 @@ hipError_t launch_reduce1d(const RedItem *items, int nitems, const SimDesc *sims
 // Grid barriers of the kernels that run whole steps (fpic_1d_steps.h).
 // cnt: zeroed counters in the workspace that only these kernels write: one
 // per 16 workgroups and one over those, the arrivals, the decision which of a
-// launch's workgroups do the work, and the counter of those if they are not all.  launch, gen: launches and
-// barriers so far (every launch has a known number, so that the counters are
-// never cleared).  arrive_ticks: how long (in 10 ns) a workgroup waits for
-// the others to be resident before those that are do the work.  bar_ticks: how long a resident workgroup then
-// waits at a barrier before it gives up (every workgroup is resident, so a
-// wait is microseconds).  failed: set (host memory, and the word kBarBad of
-// cnt) if one gave up, after which no result of the context is valid: the
-// launch leaves NaN as its state, and later launches do nothing.
+// launch's workgroups do the work, and the counter of those if they are not
+// all.  launch, gen: launches and barriers so far (every launch has a known
+// number, so that the counters are never cleared).  arrive_ticks: how long (in
+// 10 ns) a workgroup waits for the others to be resident before those that are
+// do the work.  bar_ticks: how long one of these then waits at a barrier before
+// it gives up (all are resident, so a wait is microseconds).  failed: set (host
+// memory, and the word kBarBad of cnt) if one gave up, after which no result of
+// the context is valid: the launch leaves NaN as its state, and later launches
+// do nothing.
 constexpr int kBarStride = 64, kBarGroup = 16, kMaxStepWgs = 256, kMinStepCells = 16;
 constexpr int kBarArrive = kBarStride * (1 + kMaxStepWgs / kBarGroup), kBarMode = kBarArrive + kBarStride;
 constexpr int kBarBad = kBarMode + kBarStride, kBarTeam = kBarBad + kBarStride, kBarWords = kBarTeam + kBarStride;

@@ -71,8 +71,9 @@ constexpr int BLK = 256;            // particles (threads) per workgroup
 constexpr int NWAVE = BLK / 64;
 // LDS of a stage workgroup (8-byte words): the grid cells it interpolates
 // from, then the particle records and box accumulators of its deposit.  Two
-// workgroups of a 3D box fit a CU (its stage kernels need more than 168
-// registers a lane), three of a 1D box.
+// workgroups fit a CU: the stage kernels take 173 to 256 registers a lane, two
+// waves per SIMD (of a 1D box three would find room in LDS; its moment kernels,
+// at 46 to 78 registers, run three).
 template <bool D3, bool EXACT>
 constexpr int acc_words() { return D3 ? (EXACT ? 9952 : 8192) : (EXACT ? 6400 : 6144); }
 constexpr int MAX_COPIES = 32;      // replicas of the box accumulator
@@ -690,11 +691,12 @@ __device__ __forceinline__ KeyRange key_range(int key, bool active, int nc, int 
 // EXACT: deposits summed exactly in the limbs (finalize_kernel then writes
 // the grid); otherwise with floating-point atomics straight into the grid.
 //
-// Two waves per SIMD for every shape.  With the quadratic shape that costs
-// registers (the 3D kernels spill 130-330 bytes per lane to scratch memory)
-// but against one wave per SIMD it is still faster: exact sums on the random
-// 2048-cell box 0.737 -> 0.613 ms per step, on the random 32^3 box 21.2 ->
-// 14.6 ms.
+// Two waves per SIMD for every shape.  In 3D that costs registers (the
+// quadratic kernels spill 216-384 bytes per lane to scratch memory, the linear
+// stage 4 92) but against one wave per SIMD it is still faster, ms per step
+// with exact sums: random 2048-cell box of 378 a cell 0.412 -> 0.407,
+// quadratic 0.448 -> 0.444, random 32^3 box of 92 a cell 4.60 -> 4.13,
+// quadratic 15.4 -> 14.7.
 template <int MODE, int SH, bool D3, bool EXACT>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2)))
 pstage_kernel(const PDesc *__restrict__ dp, double *outG)
@@ -1439,8 +1441,10 @@ __global__ void load_kernel(const PDesc *__restrict__ dp, const double *pos0, co
 }
 
 // The state in the caller's order: component by component, or (whole lines)
-// every particle's 18 reals to its place in the set that the next sort writes,
-// and that array transposed.
+// every particle's 18 reals to its place in the slopes' arrays (K1 and the
+// start of K2, which only the stages of one step use), and that transposed.  Not
+// in the other set of particles: replayed from a captured graph after a sort,
+// that would be the one the steps go on with.
 __global__ void unload_kernel(const PDesc *__restrict__ dp, double *out)
 {
     const PDesc &S = *dp;
@@ -1474,7 +1478,7 @@ __global__ void __launch_bounds__(BLK) unload_rows_kernel(const PDesc *__restric
     __syncthreads();
     for (int q = t; q < 18 * m; q += BLK) {
         const int p = q / 18, k = q - 18 * p;
-        gst(S.Y2 + (int64_t)sid[p] * 18 + k, sh[p * UST + k]);
+        gst(S.K1 + (int64_t)sid[p] * 18 + k, sh[p * UST + k]);
     }
 }
 
@@ -1486,7 +1490,7 @@ __global__ void __launch_bounds__(BLK) unload_transpose_kernel(const PDesc *__re
     const int t = threadIdx.x, m = (int)min((int64_t)BLK, np - base);
     for (int q = t; q < 18 * m; q += BLK) {
         const int p = q / 18, k = q - 18 * p;
-        sh[p * UST + k] = fpic::gld_nt(S.Y2 + base * 18 + q);
+        sh[p * UST + k] = fpic::gld_nt(S.K1 + base * 18 + q);
     }
     __syncthreads();
     if (t < m)
@@ -1668,7 +1672,7 @@ static int layout(const fpic_pconfig &c, Layout &L)
         L.set[s][5] = take(sizeof(int32_t) * np);
     }
     L.K1 = take(d * fpic::NK * np);
-    L.K2 = take(d * fpic::NK * np);
+    L.K2 = take(d * fpic::NK * np);  // (right behind K1: see unload_rows_kernel)
     L.K3 = take(d * fpic::NK * np);
     for (int g = 0; g < 3; ++g)
         L.G[g] = take(d * NG * nc);

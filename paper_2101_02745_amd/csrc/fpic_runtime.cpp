@@ -150,25 +150,26 @@ bool is_1d(const fpic_config &c) { return c.ncell[0] == 1 && c.ncell[1] == 1; }
 
 // The launch shape where the caller leaves it open (waves or dpw zero).  A
 // workgroup stages its grid tiles and sums its waves' deposits once, about as
-// long as kFixed directions take, and each of its waves sweeps dpw
-// directions; the chip holds 8 waves per CU (the stage kernels use 211-254
-// registers), so a launch takes ceil(workgroups / slots) rounds of dpw +
-// kFixed.  The shape with the fewest is taken: up to one workgroup of 8 waves
-// on each of the 256 CUs, then longer waves.  Against 4 waves and about 1024
-// workgroups, us per step: 2048 x 378 285 -> 202, 1000 x 378 209 -> 137,
-// 4096 x 128 239 -> 164, 512 x 128 90 -> 81, 777 x 92 quadratic 147 -> 116,
-// 5000 x 378 565 -> 467, 24 boxes of 11.5 M particles 3958 -> 3094 (those
-// measured fastest in a sweep of 1-8 waves and 1-24 directions).  Workgroups
-// of 4 waves stage twice as many tiles per CU (219 us for the 2048 x 378 box)
-// and pay where their smaller granularity saves a round.  A single box gets
-// at most the workgroups (and partial sums) of the caller's waves, or 4, in
-// about 1024 of them: fpic_step_noalloc's fixed scratch, which takes the same
-// shape, holds every box up to the size its limit states.  With several
-// directions a wave given, 4 waves are taken: 8 make fewer workgroups of longer
-// waves (us per step, 4 against 8: 200 x 92 with 4 directions 170, 230; 512 x
-// 128 with 4 117, 139, with 12 236, 291; 2048 x 378 with 12 268, 308, with 4
-// 293, 284), and from 51 directions a wave on those of a quadratic box pass the
-// LDS.
+// long as 1.5 directions take (2.5 in workgroups of up to 4 waves), and each of
+// its waves sweeps dpw directions; the chip holds 8 waves per CU (the stage
+// kernels use 211-254 registers), so a launch takes ceil(workgroups / slots)
+// rounds of dpw and that.  The shape with the fewest is taken: up to one
+// workgroup of 8 waves on each of the 256 CUs (of this chip; not asked of the
+// device, since a plan and its workspace are the same on any), then longer
+// waves.  Against 4 waves and about 1024 workgroups, us per step: 2048 x 378
+// 285 -> 202, 1000 x 378 209 -> 137, 4096 x 128 239 -> 164, 512 x 128 90 -> 81,
+// 777 x 92 quadratic 147 -> 116, 5000 x 378 565 -> 467, 24 boxes of 11.5 M
+// particles 3958 -> 3094 (those measured fastest in a sweep of 1-8 waves and
+// 1-24 directions).  Workgroups of 4 waves stage twice as many tiles per CU
+// (219 us for the 2048 x 378 box) and pay where their smaller granularity saves
+// a round.  A single box gets at most the workgroups (and partial sums) of the
+// caller's waves, or 4, in about 1024 of them: fpic_step_noalloc's fixed
+// scratch, which takes the same shape, holds every box up to the size its limit
+// states.  With several directions a wave given, 4 waves are taken: 8 make
+// fewer workgroups of longer waves (us per step, 4 against 8: 200 x 92 with 4
+// directions 170, 230; 512 x 128 with 4 117, 139, with 12 236, 291; 2048 x 378
+// with 12 268, 308, with 4 293, 284), and from 51 directions a wave on those of
+// a quadratic box pass the LDS.
 void choose_shape(int nsim, const fpic_config *cfgs, int &waves, int &dpw)
 {
     constexpr int kCus = 256;
@@ -505,8 +506,7 @@ int run_steps(fpic_batch *b, const SimDesc *ds, int stride, int keep, int nsteps
     }
     std::lock_guard<std::mutex> lock(g_steps_mu);
     b->launching = false;
-    HIPCHECK(e);
-    return FPIC_OK;
+    return e == hipSuccess ? FPIC_OK : fail(FPIC_EHIP, std::string("step launch: ") + hipGetErrorString(e));
 }
 
 }  // namespace
