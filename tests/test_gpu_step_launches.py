@@ -298,3 +298,53 @@ def test_steps_while_the_stream_is_captured():
     assert got[0][0] == got[1][0]
     assert torch.equal(got[0][1], got[1][1])
     assert torch.equal(got[0][1], reference(w, got[0][0] - 4, 4))
+
+
+@pytest.mark.parametrize("nz,ndir,shape", [(16, 26, 1), (65, 26, 2), (130, 64, 1), (200, 92, 2)])
+@pytest.mark.parametrize("step0", [0, 10 ** 9])
+def test_fast_particles(nz, ndir, shape, step0):
+    """Steps of nearly two cells: most anchors move on in every half step."""
+    w = box(nz, ndir, shape, dz=0.0505)
+    s = Sim.from_workload(w)
+    s.set_state(state(w), step0)
+    s.step(7)
+    s.step(4)
+    s.sync()
+    assert launches(s) == 2
+    assert torch.equal(s.get_state(), reference(w, 11, step0))
+
+
+def test_threads():
+    """Contexts on streams of their own, stepped by a thread each, together
+    larger than the chip: every one as if it were alone."""
+    import threading
+    ws = [box(2048, 64, 1), box(777, 92, 1), box(2000, 60, 2), box(200, 92, 1), box(32, 26, 1), box(130, 24, 2)]
+    sims, errors = [], []
+    for w in ws:
+        with torch.cuda.stream(torch.cuda.Stream()):
+            sims.append(Sim.from_workload(w))
+            sims[-1].set_state(state(w))
+            sims[-1].sync()
+
+    def work(s, seed):
+        try:
+            for k in range(40):
+                s.step(1 + (k * seed) % 4)
+                if k % 7 == seed % 7:
+                    s.sync()
+            s.sync()
+        except Exception as e:          # (an exception in a thread would be lost)
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(s, i + 1)) for i, s in enumerate(sims)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors
+    for i, (s, w) in enumerate(zip(sims, ws)):
+        n = sum(1 + (k * (i + 1)) % 4 for k in range(40))
+        got = s.get_state()
+        s.sync()
+        assert s.step_index() == n
+        assert torch.equal(got, reference(w, n))
