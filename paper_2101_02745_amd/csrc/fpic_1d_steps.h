@@ -40,9 +40,9 @@ typedef __attribute__((address_space(1))) unsigned guint;
 // Waits until counter c has reached target; false if the wait was given up.
 __device__ __forceinline__ bool reached(const GridBar &b, guint *c, unsigned target)
 {
-    const unsigned long long t0 = wall_clock64();
+    const unsigned t0 = (unsigned)wall_clock64();
     while ((int)(__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
-        if (wall_clock64() - t0 > b.bar_ticks)
+        if (__builtin_expect((unsigned)wall_clock64() - t0 > b.bar_ticks, 0))
             return false;
         __builtin_amdgcn_s_sleep(1);
     }
@@ -306,9 +306,10 @@ __device__ __forceinline__ int64_t particle_at(const Item &I, const Shift &s)
 // steps of the 2048 x 64 box, with the host's wait, 700 us by 140 to 190 of its
 // 256 workgroups, against 436 by all.  The four stages are one body (mode is
 // uniform): a body for each was 36 KB of code a stage, more than the
-// instruction cache holds for a step.  False if a barrier's wait was given up.
+// instruction cache holds for a step.  Ends early, with sflag 0, where a
+// barrier's wait was given up.
 template <int SH, bool SHARED>
-__device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, const SimDesc *__restrict__ sims,
+__device__ __forceinline__ void all_steps(const WorkItem *__restrict__ work, const SimDesc *__restrict__ sims,
                                           int stride, int keep, int nsteps, const GridBar &bar, const Lds &L,
                                           Columns &C, int *sflag, const Team &team, int wave, int lane, int nwaves)
 {
@@ -345,7 +346,7 @@ __device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, con
             if (last && !I.first) {
                 if (SHARED)
                     continue;
-                return true;
+                return;
             }
             const cSimDesc &S = I.ds[(int64_t)st * stride];
             const int64_t n = n0 + (it >> 2), np = S.np;
@@ -551,9 +552,8 @@ __device__ __forceinline__ bool all_steps(const WorkItem *__restrict__ work, con
         // writes the step counters)
         if (SHARED ? !team_sync(bar, team, (unsigned)it + 1u, sflag)
                    : !last && !grid_sync(bar, bar.gen + (unsigned)it + 1u, sflag))
-            return false;
+            return;
     }
-    return true;
 }
 
 // After a wait that was given up: the failure words, then NaN in every state
@@ -639,7 +639,7 @@ steps1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ si
                int nsteps, GridBar bar)
 {
     extern __shared__ double smem[];
-    __shared__ int sflag[2];
+    __shared__ int sflag, tflag[2];
     __shared__ Columns C;
     const int lane = threadIdx.x & (TILE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / TILE);
@@ -651,15 +651,14 @@ steps1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ si
     L.eb = L.xc + nwaves * 9 * TILE;
     L.v = L.eb + nwaves * 9 * n_edges(SH);
     L.pass = L.v + nwaves * 4 + wave * kPart;  // this wave's
-    const Team team = team_of(bar, sflag);
+    const Team team = team_of(bar, tflag);
     if (team.rank >= team.size)
         return;
-    bool ok;
     if (team.size == gridDim.x) {
-        ok = all_steps<SH, false>(work, sims, stride, keep, nsteps, bar, L, C, sflag, team, wave, lane, nwaves);
+        all_steps<SH, false>(work, sims, stride, keep, nsteps, bar, L, C, &sflag, team, wave, lane, nwaves);
     } else {
-        ok = all_steps<SH, true>(work, sims, stride, keep, nsteps, bar, L, C, sflag, team, wave, lane, nwaves);
-        if (ok && team.rank == 0) {
+        all_steps<SH, true>(work, sims, stride, keep, nsteps, bar, L, C, &sflag, team, wave, lane, nwaves);
+        if (sflag != 0 && team.rank == 0) {
             // the step counters, and the barriers that the next launch counts on
             for (int q = threadIdx.x; q < (int)gridDim.x; q += blockDim.x)
                 if (work[q].tile == 0 && work[q].group == 0)
@@ -673,7 +672,7 @@ steps1d_kernel(const WorkItem *__restrict__ work, const SimDesc *__restrict__ si
                 __hip_atomic_fetch_add((guint *)bar.cnt, nbar * ngrp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    if (!ok)
+    if (sflag == 0)  // (as the latest barrier left it; every launch has one)
         give_up(bar, work, sims, (nsteps - 1) * stride);
 }
 

@@ -129,8 +129,9 @@ constexpr int kBarBad = kBarMode + kBarStride, kBarTeam = kBarBad + kBarStride, 
 struct GridBar {
     unsigned *cnt;
     unsigned launch, gen;
-    unsigned long long arrive_ticks, bar_ticks;
+    unsigned long long arrive_ticks;
     int *failed;
+    unsigned bar_ticks;
 };
 // nsteps steps of every box (4 nsteps barriers) in one launch of one
 // workgroup per work item, one direction per wave; step j uses the
@@ -169,6 +170,6 @@ int fail(int code, const std::string &msg);
 struct fpic_ctx;
 struct fpic_batch;
 extern "C" int fpic_test_step_waits(fpic_ctx *ctx, fpic_batch *batch, unsigned long long arrive_ticks,
-                                    unsigned long long bar_ticks);
+                                    unsigned bar_ticks);
 // For tests: launches of whole steps so far, -1 if there are none to be made.
 extern "C" int fpic_test_step_launches(fpic_ctx *ctx, fpic_batch *batch);

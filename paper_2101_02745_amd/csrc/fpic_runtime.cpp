@@ -348,7 +348,7 @@ struct fpic_batch {
     // how long its workgroups wait to be resident together before those that
     // are do the work, in ticks of 10 ns (kArriveRule: see run_steps)
     unsigned long long arrive_ticks = kArriveRule;
-    unsigned long long bar_ticks = 2000000000ull;  // and at a barrier before it gives up (20 s)
+    unsigned bar_ticks = 2000000000u;  // and at a barrier before it gives up (20 s)
     int device = 0;
     double cell_volume = 1.0;      // of simulation 0
     // reverse mode (single 1D box)
@@ -496,8 +496,8 @@ int run_steps(fpic_batch *b, const SimDesc *ds, int stride, int keep, int nsteps
     const Plan &P = b->plan;
     const unsigned long long arrive =
         b->arrive_ticks == kArriveRule ? 300000ull + 10000ull * (unsigned)nsteps : b->arrive_ticks;
-    const GridBar bar{reinterpret_cast<unsigned *>(b->ws + P.o_bar), b->launches, b->gen, arrive, b->bar_ticks,
-                      reinterpret_cast<int *>(b->hbuf + kFailed)};
+    const GridBar bar{reinterpret_cast<unsigned *>(b->ws + P.o_bar), b->launches, b->gen, arrive,
+                      reinterpret_cast<int *>(b->hbuf + kFailed), b->bar_ticks};
     hipError_t e = launch_steps1d(b->dwork, P.nwork, ds, stride, keep, P.waves, P.shape, nsteps, bar, b->stream);
     if (e == hipSuccess) {
         b->launches += 1u;
@@ -523,7 +523,7 @@ int fpic::set_arrive_ticks(void *ctx, unsigned long long ticks)
 }
 
 extern "C" int fpic_test_step_waits(fpic_ctx *ctx, fpic_batch *batch, unsigned long long arrive_ticks,
-                                    unsigned long long bar_ticks)
+                                    unsigned bar_ticks)
 {
     fpic_batch *b = ctx ? ctx->b : batch;
     if (!b || !b->steps)

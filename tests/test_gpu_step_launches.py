@@ -25,7 +25,7 @@ def reference(w, steps, step0=0):
 
 def set_waits(s, arrive, barrier):
     f = _lib.load().fpic_test_step_waits
-    f.argtypes = [C.c_void_p, C.c_void_p, C.c_uint64, C.c_uint64]
+    f.argtypes = [C.c_void_p, C.c_void_p, C.c_uint64, C.c_uint32]
     check(f(getattr(s, "ctx", None), getattr(s, "b", None), arrive, barrier))
 
 
